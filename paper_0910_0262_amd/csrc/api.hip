@@ -15,16 +15,11 @@
 #include "cloverqcd.h"
 #include "qcd_internal.h"
 
-// Fixed device scratch of the allocation-free entry point
-// (qcd_gauge_force_noalloc): the gauge-force accumulator [mu][parity][9][Vh]
-// of a lattice of at most kScratchVh checkerboard sites.  Each GPU the
-// library runs on holds its own copy from module load to process end; every
-// call on that GPU shares it.  Host code never passes `scratch` itself to a
-// kernel (that is a host-side stand-in); it uses the per-device address
-// hipGetSymbolAddress returns.
-static constexpr size_t kScratchBytes = (size_t)64 << 20;
-static constexpr size_t kScratchVh = kScratchBytes / (8 * 9 * sizeof(double2));
-static __device__ __align__(256) double2 scratch[kScratchBytes / sizeof(double2)];
+// Lattice limit of the allocation-free entry point (qcd_gauge_force_noalloc),
+// part of its contract: the checkerboard sites whose force accumulator (576
+// bytes per site pair of links) would fit 64 MiB.
+static constexpr size_t kNoallocBytes = (size_t)64 << 20;
+static constexpr size_t kNoallocVh = kNoallocBytes / (8 * 9 * sizeof(double2));
 
 using namespace qcd;
 
@@ -124,9 +119,9 @@ struct qcd_ctx {
   hipGraphExec_t iter_graph[2][4] = {};  // one CG iteration: [FP64, mixed][position in the x cycle]
   int* status = nullptr;
   int* status_host = nullptr;  // pinned
-  double2* xi = nullptr;       // clover-force Xi: [par][6][9][stride]
+  double2* xi = nullptr;       // clover-force Xi: [par][6][kXiChunks][stride]
   double2* gint = nullptr;     // force accumulator: [mu][par][9][stride]
-  double* fbuf = nullptr;      // su(3) force [V][4][8] for the HMD step
+  double* md_partial = nullptr;  // partial sums of the molecular-dynamics kernels, then their span sums
   double* logdet = nullptr;    // ln det A(x) per odd site, from the last clover inversion
 
   // Workgroup size of the stencils and reductions, measured: 64 threads for
@@ -256,7 +251,7 @@ void free_ctx(qcd_ctx* c) {
   f(c->status);
   f(c->xi);
   f(c->gint);
-  f(c->fbuf);
+  f(c->md_partial);
   f(c->logdet);
   if (c->status_host) (void)hipHostFree(c->status_host);
   for (auto& row : c->iter_graph)
@@ -267,32 +262,12 @@ void free_ctx(qcd_ctx* c) {
     if (e) (void)hipEventDestroy(e);
 }
 
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-double2* g_scratch_dev[kMaxDevices] = {};  // device address of `scratch`, per device
-
 // the site term of k2 reads the compact A_ee where the clover term has its form
 bool use_compact(const qcd_ctx* c) { return c->compact_clover == 1 && c->compact_ok; }
 int check_ctx(qcd_ctx* c) {
   if (!c) return fail(QCD_EINVAL, "null context");
   if (hipSetDevice(c->device) != hipSuccess) return fail(QCD_EHIP, "hipSetDevice failed");
   return QCD_OK;
-}
-// Resolve the device address of `scratch` on device `dev` (current), once per device.
-int resolve_scratch(int dev) {
-  if (dev >= kMaxDevices) return fail(QCD_EINVAL, "device index beyond the library's table");
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (g_scratch_dev[dev]) return QCD_OK;
-  void* p = nullptr;
-  const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-  if (e != hipSuccess || p == nullptr)
-    return fail(QCD_EHIP, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-  g_scratch_dev[dev] = static_cast<double2*>(p);
-  return QCD_OK;
-}
-double2* scratch_of(int dev) {
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  return dev < kMaxDevices ? g_scratch_dev[dev] : nullptr;
 }
 int need_gauge(qcd_ctx* c) {
   if (!c->gauge_loaded) return fail(QCD_ESTATE, "no gauge field loaded");
@@ -864,7 +839,6 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev)
     return fail(QCD_EINVAL, "device " + std::to_string(device) + " not available");
   HIPCHK(hipSetDevice(device));
-  QCHK(resolve_scratch(device));
   qcd_ctx* c = new qcd_ctx();
   for (int k = 0; k < 4; ++k) c->dims[k] = dims[k];
   c->device = device;
@@ -901,6 +875,7 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   A(&c->clovhc_e, 6 * S * sizeof(uint4) + S * sizeof(uint2));
   A(&c->clovhc_es, S * sizeof(float2));
   A(&c->status, 2 * sizeof(int));
+  A(&c->md_partial, (md_link_partials(g) + md_link_partials(g) / kFoldSpan + 1) * sizeof(double));
   if (rc == QCD_OK) rc = alloc_work(g, c->w1, 0, true);
   if (rc == QCD_OK && hipHostMalloc((void**)&c->status_host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess)
     rc = fail(QCD_ENOMEM, "pinned host allocation failed");
@@ -1232,15 +1207,24 @@ int qcd_solve_multi(qcd_ctx* c, const qcd_solver_params* p, int n_rhs, const voi
   return rc;
 }
 
+// Buffers of the fermion and determinant forces (the gauge force needs none).
+static int ensure_force_buffers(qcd_ctx* c) {
+  const Geom& g = c->g;
+  if (!c->xi) QCHK(dalloc(&c->xi, (size_t)2 * 6 * kXiChunks * g.stride * sizeof(double2)));
+  if (!c->gint) QCHK(dalloc(&c->gint, (size_t)8 * 9 * g.stride * sizeof(double2)));
+  return QCD_OK;
+}
+
 // Force pipeline on the current context state; phi in V_RHS (even sites).
 // The fermion part of the force enters with weight wf; with det the
-// derivative of -2 sum_odd ln det A, also weighted wf, joins the clover part.
+// derivative of -2 sum_odd ln det A, also weighted wf, joins the clover part,
+// and with gauge_coef != 0 the Wilson gauge force, whose action's partial sums
+// then go to md_partial.  The last pass puts G where `out` says.
 static int force_core(qcd_ctx* c, const qcd_solver_params* p, double* S, CgCounters& cnt, int* conv_rc,
-                      double wf = 1.0, bool det = false, double gauge_coef = 0.0) {
+                      const MdOut& out, double wf = 1.0, bool det = false, double gauge_coef = 0.0) {
   const Geom& g = c->g;
   const int nb = nblocks(c);
-  if (!c->xi) QCHK(dalloc(&c->xi, (size_t)2 * 6 * 9 * g.stride * sizeof(double2)));
-  if (!c->gint) QCHK(dalloc(&c->gint, (size_t)8 * 9 * g.stride * sizeof(double2)));
+  QCHK(ensure_force_buffers(c));
   // keep phi: the solver overwrites work slots but not V_RHS
   int rc = run_cg(c, p, cnt);
   if (rc != QCD_OK) return rc;
@@ -1266,12 +1250,16 @@ static int force_core(qcd_ctx* c, const qcd_solver_params* p, double* S, CgCount
     HIPCHK(launch_dslash(g, op, c->block(), c->stream));
   }
   const double k2 = c->kappa * c->kappa;
-  HIPCHK(launch_force_hop(g, c->u18, c->f64(V_Y), c->f64(V_W), c->f64(V_X), c->f64(V_Z), 2.0 * k2 * wf, c->gint,
-                          c->stream));
+  HIPCHK(launch_force_hop(g, c->f64(V_Y), c->f64(V_W), c->f64(V_X), c->f64(V_Z), 2.0 * k2 * wf, c->gint, c->stream));
   if (c->csw != 0.0) {
     HIPCHK(launch_clover_xi(g, c->f64(V_Y), c->f64(V_W), c->f64(V_X), c->f64(V_Z), wf, wf * k2,
                             det ? c->clov_inv : nullptr, wf, c->xi, c->stream));
-    HIPCHK(launch_force_clover(g, c->u18, c->xi, 0.5 * c->kappa * c->csw, c->gint, c->stream, gauge_coef));
+    HIPCHK(launch_force_clover(g, c->u18, c->xi, 0.5 * c->kappa * c->csw, gauge_coef, c->gint, out, c->md_partial,
+                               c->stream));
+  } else if (gauge_coef != 0.0) {
+    HIPCHK(launch_gauge_force(g, c->u18, gauge_coef, c->gint, out, c->md_partial, c->stream));
+  } else {
+    HIPCHK(launch_force_finish(g, c->u18, c->gint, out, c->stream));
   }
   return QCD_OK;
 }
@@ -1286,8 +1274,10 @@ int qcd_action_force(qcd_ctx* c, const qcd_solver_params* p, const void* phi_dev
   HIPCHK(launch_pack_spinor_cb(c->g, (const double2*)phi_dev, c->f64(V_RHS), c->stream));
   CgCounters cnt;
   int conv = QCD_OK;
-  QCHK(force_core(c, p, S, cnt, &conv));
-  HIPCHK(launch_force_out(c->g, c->u18, c->gint, (double2*)G_dev, F_dev, c->stream));
+  MdOut out;
+  out.g_user = (double2*)G_dev;
+  out.f_user = F_dev;
+  QCHK(force_core(c, p, S, cnt, &conv, out));
   if (X_dev) HIPCHK(launch_unpack_spinor_cb(c->g, c->f64(V_X), (double2*)X_dev, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -1304,8 +1294,7 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
   if (!std::isfinite(dt)) return fail(QCD_EINVAL, "dt must be finite");
   const auto t0 = std::chrono::steady_clock::now();
   const Geom& g = c->g;
-  if (!c->fbuf) QCHK(dalloc(&c->fbuf, (size_t)32 * g.V * sizeof(double)));
-  if (!c->gint) QCHK(dalloc(&c->gint, (size_t)8 * 9 * g.stride * sizeof(double2)));
+  QCHK(ensure_force_buffers(c));
   // two flavours per pseudofermion at N_f = 2: the R algorithm draws the
   // noise at the start of the step, phi = Mhat^dag(U_0) xi
   HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, c->stream));
@@ -1321,10 +1310,11 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
   QCHK(qcd_build_clover(c));
   CgCounters cnt;
   int conv = QCD_OK;
-  QCHK(force_core(c, p, S, cnt, &conv));
-  HIPCHK(launch_force_out(g, c->u18, c->gint, nullptr, c->fbuf, c->stream));
   // P <- P - dt F;  U <- exp(i dt/2 P) U_1/2
-  HIPCHK(launch_mom_update(g, P_dev, c->fbuf, dt, c->stream));
+  MdOut out;
+  out.p_user = P_dev;
+  out.dt = dt;
+  QCHK(force_core(c, p, S, cnt, &conv, out));
   HIPCHK(launch_link_exp(g, c->u18, P_dev, 0.5 * dt, c->stream));
   HIPCHK(launch_derive_links(g, c->u18, c->u12, c->uh, c->uh18, c->stream));
   HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
@@ -1335,10 +1325,11 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
   return QCD_OK;
 }
 
-// beta sum (1 - Re tr P / 3) (synchronises; overwrites the host state mirror)
+// beta times the sum of the partial sums of (1 - Re tr P / 3) in md_partial
+// (synchronises; overwrites the host state mirror)
 static int gauge_action_sync(qcd_ctx* c, double beta, double* S) {
-  HIPCHK(launch_plaquette(c->g, c->u18, c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
+  const int n = md_link_partials(c->g);
+  HIPCHK(launch_fin_scalar(c->w->st, c->md_partial, n, 1, c->md_partial + n, c->stream));
   QCHK(sync_state(c));
   *S = beta * c->w->st_host->scalar;
   return QCD_OK;
@@ -1353,23 +1344,20 @@ static int det_action_sync(qcd_ctx* c, double* S) {
   return QCD_OK;
 }
 
-static int ensure_force_buffers(qcd_ctx* c) {
-  const Geom& g = c->g;
-  if (!c->xi) QCHK(dalloc(&c->xi, (size_t)2 * 6 * 9 * g.stride * sizeof(double2)));
-  if (!c->gint) QCHK(dalloc(&c->gint, (size_t)8 * 9 * g.stride * sizeof(double2)));
-  return QCD_OK;
-}
-
 int qcd_gauge_action_force(qcd_ctx* c, double beta, double* S, void* G_dev, double* F_dev) {
   QCHK(check_ctx(c));
   if (!std::isfinite(beta)) return fail(QCD_EINVAL, "beta must be finite");
   QCHK(need_gauge(c));
-  QCHK(ensure_force_buffers(c));
-  if (S) QCHK(gauge_action_sync(c, beta, S));
   if (G_dev || F_dev) {
-    HIPCHK(launch_gauge_force(c->g, c->u18, -beta / 3.0, 0, c->gint, c->stream));
-    HIPCHK(launch_force_out(c->g, c->u18, c->gint, (double2*)G_dev, F_dev, c->stream));
+    // the staples give the action too
+    MdOut out;
+    out.g_user = (double2*)G_dev;
+    out.f_user = F_dev;
+    HIPCHK(launch_gauge_force(c->g, c->u18, -beta / 3.0, nullptr, out, S ? c->md_partial : nullptr, c->stream));
+  } else if (S) {
+    HIPCHK(launch_plaquette(c->g, c->u18, c->md_partial, c->stream));
   }
+  if (S) return gauge_action_sync(c, beta, S);
   HIPCHK(hipStreamSynchronize(c->stream));
   return QCD_OK;
 }
@@ -1379,16 +1367,13 @@ int qcd_gauge_force_noalloc(qcd_ctx* c, double beta, void* G_dev, double* F_dev)
   if (!std::isfinite(beta)) return fail(QCD_EINVAL, "beta must be finite");
   if (!G_dev && !F_dev) return fail(QCD_EINVAL, "G_dev and F_dev are both null");
   QCHK(need_gauge(c));
-  if ((size_t)c->g.stride > kScratchVh)
+  if ((size_t)c->g.stride > kNoallocVh)
     return fail(QCD_EINVAL, "lattice too large for the allocation-free gauge force: " + std::to_string(c->g.V) +
-                                " sites need " + std::to_string((size_t)8 * 9 * c->g.stride * sizeof(double2)) +
-                                " bytes of scratch, the library holds " + std::to_string(kScratchBytes) +
-                                " (at most " + std::to_string(2 * kScratchVh) + " sites)");
-  double2* acc = scratch_of(c->device);
-  if (!acc) return fail(QCD_ESTATE, "scratch address not resolved on this device");
-  // the accumulator is overwritten (not accumulated) for every link: nothing to clear
-  HIPCHK(launch_gauge_force(c->g, c->u18, -beta / 3.0, 0, acc, c->stream));
-  HIPCHK(launch_force_out(c->g, c->u18, acc, (double2*)G_dev, F_dev, c->stream));
+                                " sites (at most " + std::to_string(2 * kNoallocVh) + ")");
+  MdOut out;
+  out.g_user = (double2*)G_dev;
+  out.f_user = F_dev;
+  HIPCHK(launch_gauge_force(c->g, c->u18, -beta / 3.0, nullptr, out, nullptr, c->stream));
   return QCD_OK;
 }
 
@@ -1399,13 +1384,16 @@ int qcd_clover_det_action_force(qcd_ctx* c, double* S, void* G_dev, double* F_de
   if (S) QCHK(det_action_sync(c, S));
   if (G_dev || F_dev) {
     const Geom& g = c->g;
-    HIPCHK(launch_force_zero(g, c->gint, c->stream));
+    MdOut out;
+    out.g_user = (double2*)G_dev;
+    out.f_user = F_dev;
     if (c->csw != 0.0) {
       HIPCHK(launch_clover_xi(g, SpF64{nullptr, g.stride}, SpF64{nullptr, g.stride}, SpF64{nullptr, g.stride},
                               SpF64{nullptr, g.stride}, 0.0, 0.0, c->clov_inv, 1.0, c->xi, c->stream));
-      HIPCHK(launch_force_clover(g, c->u18, c->xi, 0.5 * c->kappa * c->csw, c->gint, c->stream));
+      HIPCHK(launch_force_clover(g, c->u18, c->xi, 0.5 * c->kappa * c->csw, 0.0, nullptr, out, nullptr, c->stream));
+    } else {
+      HIPCHK(launch_force_finish(g, c->u18, nullptr, out, c->stream));
     }
-    HIPCHK(launch_force_out(g, c->u18, c->gint, (double2*)G_dev, F_dev, c->stream));
   }
   HIPCHK(hipStreamSynchronize(c->stream));
   return QCD_OK;
@@ -1440,8 +1428,7 @@ int qcd_md_trajectory(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* 
   const auto t0 = std::chrono::steady_clock::now();
   const Geom& g = c->g;
   const double dt = md->dt;
-  QCHK(ensure_force_buffers(c));
-  if (!c->fbuf) QCHK(dalloc(&c->fbuf, (size_t)32 * g.V * sizeof(double)));
+  if (ferm) QCHK(ensure_force_buffers(c));
   HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, c->stream));
   QCHK(move_links(c, P_dev, 0.0, false));  // the derived link copies of U_0
   CgCounters cnt;
@@ -1464,22 +1451,23 @@ int qcd_md_trajectory(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* 
     } else {
       QCHK(move_links(c, P_dev, 0.5 * dt, false));
     }
-    if (md->beta != 0.0) QCHK(gauge_action_sync(c, md->beta, &s_g));
     if (det) QCHK(det_action_sync(c, &s_d));
-    // with a clover force pass the gauge force is added there (its staples
-    // are products that pass forms anyway); otherwise it has its own launch
-    const bool gauge_fused = ferm && c->csw != 0.0 && md->beta != 0.0;
+    // P <- P - dt F in the last force pass; the gauge force joins it, and
+    // leaves the gauge action's partial sums
+    const double gauge_coef = md->beta != 0.0 ? -md->beta / 3.0 : 0.0;
+    MdOut out;
+    out.p_user = P_dev;
+    out.dt = dt;
     if (ferm) {
       int conv = QCD_OK;
-      QCHK(force_core(c, p, &s_f, cnt, &conv, wf, det, gauge_fused ? -md->beta / 3.0 : 0.0));
+      QCHK(force_core(c, p, &s_f, cnt, &conv, out, wf, det, gauge_coef));
       if (conv != QCD_OK) conv_all = conv;
+    } else if (gauge_coef != 0.0) {
+      HIPCHK(launch_gauge_force(g, c->u18, gauge_coef, nullptr, out, c->md_partial, c->stream));
     } else {
-      HIPCHK(launch_force_zero(g, c->gint, c->stream));
+      HIPCHK(launch_force_finish(g, c->u18, nullptr, out, c->stream));
     }
-    if (md->beta != 0.0 && !gauge_fused)
-      HIPCHK(launch_gauge_force(g, c->u18, -md->beta / 3.0, 1, c->gint, c->stream));
-    HIPCHK(launch_force_out(g, c->u18, c->gint, nullptr, c->fbuf, c->stream));
-    HIPCHK(launch_mom_update(g, P_dev, c->fbuf, dt, c->stream));
+    if (md->beta != 0.0 && actions) QCHK(gauge_action_sync(c, md->beta, &s_g));
     QCHK(move_links(c, P_dev, 0.5 * dt, md->reunitarize == 1));
     if (actions) {
       actions[3 * k] = s_f;

@@ -13,116 +13,147 @@
 
 namespace qcd {
 
-// Each link enters the leaves of many sites: ordinary (cached) loads.
-__device__ __forceinline__ Mat<double> link_at(const double2* u18, const Geom& g, int mu, const int x[4]) {
-  const double2* base = u18 + (size_t)((mu * 2 + parity_of(x)) * 9) * g.stride + (lex(x, g) >> 1);
-  Mat<double> u;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const double2 d = base[(size_t)k * g.stride];
-    u.m[k / 3][k % 3] = {d.x, d.y};
-  }
-  return u;
-}
-__device__ __forceinline__ void shift(const Geom& g, const int x[4], int mu, int n, int y[4]) {
-  y[0] = x[0];
-  y[1] = x[1];
-  y[2] = x[2];
-  y[3] = x[3];
-  y[mu] = (x[mu] + n + 2 * g.X[mu]) % g.X[mu];
-}
-
 // F_mu,nu(x) = traceless part of (Q - Q^dag) / (8i), Q the sum of the four
 // counter-clockwise leaves in the mu-nu plane starting at x.
-__device__ Mat<double> field_strength(const double2* u18, const Geom& g, const int x[4], int mu, int nu) {
-  int xp_mu[4], xp_nu[4], xm_mu[4], xm_nu[4], xm_mu_p_nu[4], xm_mu_m_nu[4], xp_mu_m_nu[4];
-  shift(g, x, mu, 1, xp_mu);
-  shift(g, x, nu, 1, xp_nu);
-  shift(g, x, mu, -1, xm_mu);
-  shift(g, x, nu, -1, xm_nu);
-  shift(g, xm_mu, nu, 1, xm_mu_p_nu);
-  shift(g, xm_mu, nu, -1, xm_mu_m_nu);
-  shift(g, xp_mu, nu, -1, xp_mu_m_nu);
-
-  const Mat<double> um_x = link_at(u18, g, mu, x), un_x = link_at(u18, g, nu, x);
-  Mat<double> q;
+struct FHerm {  // Hermitian 3x3: diagonal, then entries 01, 02, 12
+  double d[3];
+  Cx<double> x[3];
+};
+__device__ __forceinline__ FHerm field_strength(const double2* __restrict__ u18, const MdGeom& m,
+                                                const MdSite& s, int par, int mu, int nu) {
+  const int st = m.g.stride, np = 1 - par;
+  const int fm = md_fwd(m, s, mu), fn = md_fwd(m, s, nu), bm = md_bwd(m, s, mu), bn = md_bwd(m, s, nu);
+  auto U = [&](int d, int p, int step) { return md_link(u18, st, d, p, (s.i + step) >> 1); };
+  const Mat<double> un_x = U(nu, par, 0);
+  Mat<double> q, t;
   // U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-  q = mm(mm(um_x, link_at(u18, g, nu, xp_mu)), mm(adj(link_at(u18, g, mu, xp_nu)), adj(un_x)));
+  t = mm(U(mu, par, 0), U(nu, np, fm));
+  t = mm(t, adj(U(mu, np, fn)));
+  q = mm(t, adj(un_x));
+  __builtin_amdgcn_sched_barrier(0);
   // U_nu(x) U_mu(x-mu+nu)^dag U_nu(x-mu)^dag U_mu(x-mu)
-  const Mat<double> um_xm = link_at(u18, g, mu, xm_mu);
-  q = madd(q, mm(mm(un_x, adj(link_at(u18, g, mu, xm_mu_p_nu))), mm(adj(link_at(u18, g, nu, xm_mu)), um_xm)));
+  t = mm(un_x, adj(U(mu, par, bm + fn)));
+  t = mm(t, adj(U(nu, np, bm)));
+  const Mat<double> um_xm = U(mu, np, bm);
+  mm_acc(q, t, um_xm);
+  __builtin_amdgcn_sched_barrier(0);
   // U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_nu(x-nu)
-  const Mat<double> un_xm = link_at(u18, g, nu, xm_nu);
-  q = madd(q, mm(mm(adj(um_xm), adj(link_at(u18, g, nu, xm_mu_m_nu))), mm(link_at(u18, g, mu, xm_mu_m_nu), un_xm)));
+  t = mm(adj(um_xm), adj(U(nu, par, bm + bn)));
+  t = mm(t, U(mu, par, bm + bn));
+  const Mat<double> un_xm = U(nu, np, bn);
+  mm_acc(q, t, un_xm);
+  __builtin_amdgcn_sched_barrier(0);
   // U_nu(x-nu)^dag U_mu(x-nu) U_nu(x+mu-nu) U_mu(x)^dag
-  q = madd(q, mm(mm(adj(un_xm), link_at(u18, g, mu, xm_nu)), mm(link_at(u18, g, nu, xp_mu_m_nu), adj(um_x))));
+  t = mm(adj(un_xm), U(mu, np, bn));
+  t = mm(t, U(nu, par, fm + bn));
+  int own = s.cb;  // read again rather than kept: two wavefronts per SIMD leave no registers for it
+  asm volatile("" : "+v"(own));
+  mm_acc(q, t, adj(md_link(u18, st, mu, par, own)));
 
-  Mat<double> f;
+  FHerm f;
+  const double tr = (q.m[0][0].im + q.m[1][1].im + q.m[2][2].im) / 3.0;
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int a = 0; a < 3; ++a) f.d[a] = 0.25 * (q.m[a][a].im - tr);
+  // (q_ab - conj q_ba) / (8 i)
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const Cx<double> d = q.m[a][b] - conj(q.m[b][a]);
-      f.m[a][b] = {d.im / 8.0, -d.re / 8.0};  // d / (8 i)
-    }
-  const double tr = (f.m[0][0].re + f.m[1][1].re + f.m[2][2].re) / 3.0;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) f.m[a][a].re -= tr;
+  for (int k = 0; k < 3; ++k) {
+    const Cx<double> d = q.m[k == 2][k == 0 ? 1 : 2] - conj(q.m[k == 0 ? 1 : 2][k == 2]);
+    f.x[k] = {d.im / 8.0, -d.re / 8.0};
+  }
   return f;
 }
 
-__global__ void __launch_bounds__(64) clover_build_k(Geom g, const double2* __restrict__ u18, double kc,
-                                                     double2* __restrict__ clov) {
-  const int j = md_position();
-  if (j >= g.V) return;
-  int x[4];
-  const int i = md_site(j, g, x);
-  const int par = parity_of(x), cb = i >> 1;
-  const Mat<double> f01 = field_strength(u18, g, x, 0, 1);
-  const Mat<double> f02 = field_strength(u18, g, x, 0, 2);
-  const Mat<double> f03 = field_strength(u18, g, x, 0, 3);
-  const Mat<double> f12 = field_strength(u18, g, x, 1, 2);
-  const Mat<double> f13 = field_strength(u18, g, x, 1, 3);
-  const Mat<double> f23 = field_strength(u18, g, x, 2, 3);
-#pragma unroll 1
-  for (int b = 0; b < 2; ++b) {
-    Mat<double> X, Y, Z;
-    if (b == 0) {
-      X = msub(f03, f12);
-      Y = madd(f02, f13);
-      Z = msub(f23, f01);
-    } else {
-      X = msub(mzero<double>(), madd(f12, f03));
-      Y = msub(f02, f13);
-      Z = msub(mzero<double>(), madd(f01, f23));
+// sa a + sb b
+__device__ __forceinline__ FHerm fsum(const FHerm& a, double sa, const FHerm& b, double sb) {
+  FHerm f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    f.d[k] = sa * a.d[k] + sb * b.d[k];
+    f.x[k] = sa * a.x[k] + sb * b.x[k];
+  }
+  return f;
+}
+
+// A workgroup of six wavefronts takes 64 sites of one parity, each wavefront
+// the leaves of one plane; the six F (9 reals each) meet in LDS and each
+// wavefront then writes six of the 36 chunks of A.
+struct BuildLds {
+  double f[6][9][64];
+};
+__device__ __forceinline__ FHerm lds_f(const BuildLds& l, int p, int lane) {
+  FHerm f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    f.d[k] = l.f[p][k][lane];
+    f.x[k] = {l.f[p][3 + 2 * k][lane], l.f[p][4 + 2 * k][lane]};
+  }
+  return f;
+}
+__global__ void __launch_bounds__(384) clover_build_k(MdGeom m, const double2* __restrict__ u18, double kc,
+                                                      double2* __restrict__ clov) {
+  __shared__ BuildLds lds;
+  const Geom& g = m.g;
+  const int w = xcd_block(blockIdx.x, gridDim.x), par = w & 1;
+  const int lane = threadIdx.x & 63, p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = ((w >> 1) << 6) + lane;
+  const bool live = j < g.Vh;
+  const MdSite s = md_site(m, min(j, g.Vh - 1), par);
+  // planes 01 02 03 12 13 23
+  const int mu = p < 3 ? 0 : (p < 5 ? 1 : 2), nu = p < 3 ? p + 1 : (p < 5 ? p - 1 : 3);
+  {
+    const FHerm f = field_strength(u18, m, s, par, mu, nu);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lds.f[p][k][lane] = f.d[k];
+      lds.f[p][3 + 2 * k][lane] = f.x[k].re;
+      lds.f[p][4 + 2 * k][lane] = f.x[k].im;
     }
-    // 6x6 block entry (r, c): sub-block (r / 3, c / 3), colour (r % 3, c % 3)
-    Cx<double> blk[6][6];
+  }
+  __syncthreads();
+  if (!live) return;
+  const int h = p >= 3, part = p - 3 * h;  // chiral half, and which of its chunks
+  const double sg = h == 0 ? kc : -kc;
+  double2* const dst = clov + (size_t)(par * 36 + h * 18) * g.stride;
+  auto put = [&](int k, double a, double b) { *elem(dst, (size_t)k * g.stride, s.cb) = make_double2(a, b); };
+  // upper half X = F03 - F12, Y = F02 + F13, Z = F23 - F01;
+  // lower half X = -F03 - F12, Y = F02 - F13, Z = -F23 - F01
+  if (part < 2) {
+    const FHerm z = fsum(lds_f(lds, 5, lane), sg, lds_f(lds, 0, lane), -kc);
+    if (part == 0) {
+      put(0, 1.0 - z.d[0], 1.0 - z.d[1]);
+      put(1, 1.0 - z.d[2], 1.0 + z.d[0]);
+      put(2, 1.0 + z.d[1], 1.0 + z.d[2]);
+    }
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int k = 0; k < 3; ++k) {
+      const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;
+      if (part == 0)
+        put(3 + offd(a, b), -z.x[k].re, -z.x[k].im);
+      else
+        put(3 + offd(3 + a, 3 + b), z.x[k].re, z.x[k].im);
+    }
+  }
+  if (part > 0) {  // entries -(X - iY)
+    const FHerm x = fsum(lds_f(lds, 2, lane), sg, lds_f(lds, 3, lane), -kc);
+    const FHerm y = fsum(lds_f(lds, 1, lane), kc, lds_f(lds, 4, lane), sg);
+    if (part == 1) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const Cx<double> z = Z.m[a][c], xx = X.m[a][c], yy = Y.m[a][c];
-        const Cx<double> one = {a == c ? 1.0 : 0.0, 0.0};
-        blk[a][c] = one - kc * z;
-        blk[3 + a][3 + c] = one + kc * z;
-        blk[a][3 + c] = -kc * (xx - ti(yy));
-        blk[3 + a][c] = -kc * (xx + ti(yy));
+      for (int a = 0; a < 3; ++a) put(3 + offd(a, 3 + a), -x.d[a], y.d[a]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;
+        const Cx<double> u = ti(y.x[k]) - x.x[k], l = ti(conj(y.x[k])) - conj(x.x[k]);
+        put(3 + offd(a, 3 + b), u.re, u.im);
+        put(3 + offd(b, 3 + a), l.re, l.im);
       }
-    double2* dst = clov + (size_t)(par * 36 + b * 18) * g.stride + cb;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) dst[(size_t)k * g.stride] = make_double2(blk[2 * k][2 * k].re, blk[2 * k + 1][2 * k + 1].re);
-#pragma unroll
-    for (int r = 0; r < 6; ++r)
-#pragma unroll
-      for (int c = r + 1; c < 6; ++c)
-        dst[(size_t)(3 + offd(r, c)) * g.stride] = make_double2(blk[r][c].re, blk[r][c].im);
+    }
   }
 }
 
 hipError_t launch_clover_build(const Geom& g, const double2* u18, double kappa, double csw, double2* clov,
                                hipStream_t s) {
-  hipLaunchKernelGGL(clover_build_k, dim3(blocks_for(g.V, 64)), dim3(64), 0, s, g, u18, kappa * csw, clov);
+  hipLaunchKernelGGL(clover_build_k, dim3(md_site_blocks(g)), dim3(384), 0, s, md_geom(g), u18, kappa * csw, clov);
   return hipGetLastError();
 }
 

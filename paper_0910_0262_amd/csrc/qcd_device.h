@@ -167,13 +167,19 @@ __device__ __forceinline__ void mul_adj(const Mat<R>& u, const Half<R>& in, Half
     }
 }
 
+// a b with every rounding written out, so that it is the same wherever the
+// product is inlined (kernels that must agree to the last bit share it)
 template <typename R>
 __device__ __forceinline__ Mat<R> mm(const Mat<R>& a, const Mat<R>& b) {
   Mat<R> c;
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) c.m[i][j] = cfma(a.m[i][2], b.m[2][j], cfma(a.m[i][1], b.m[1][j], a.m[i][0] * b.m[0][j]));
+    for (int j = 0; j < 3; ++j) {
+      const Cx<R> u = a.m[i][0], v = b.m[0][j];
+      const Cx<R> p = {fmar(-u.im, v.im, u.re * v.re), fmar(u.im, v.re, u.re * v.im)};
+      c.m[i][j] = cfma(a.m[i][2], b.m[2][j], cfma(a.m[i][1], b.m[1][j], p));
+    }
   return c;
 }
 template <typename R>
@@ -976,11 +982,16 @@ __device__ __forceinline__ void accumulate(Spinor<R>& a, const Half<R>& h, R fu,
 }
 
 // ------------------------------------------------------------------ reductions
+// Sum over the wavefront, in lane 0.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  return v;
+}
 // Sum of v over the workgroup (wave64 shuffles, then LDS); the result is
 // written by thread 0 to partial[slot].  Every thread of the block must call it.
 __device__ __forceinline__ void block_sum_store(double v, double* partial, int slot) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v = wave_sum(v);
   __shared__ double red[16];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (lane == 0) red[w] = v;

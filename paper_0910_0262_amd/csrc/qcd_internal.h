@@ -218,23 +218,37 @@ hipError_t launch_clover_invert(const Geom& g, const double2* clov, double2* clo
                                 float2* clovinvh_os, double* logdet, int* status, hipStream_t s);
 
 // ---- force.hip
-hipError_t launch_force_hop(const Geom& g, const double2* u18, SpF64 ell_e, SpF64 ell_o, SpF64 rho_e,
-                            SpF64 rho_o, double coef, double2* gint, hipStream_t s);
-// ell_e.p == nullptr drops the fermion term; cinv == nullptr the determinant term
+// Where a force pass puts G (dS/dRe U + i dS/dIm U): any of the accumulator
+// [mu][par][9][stride], the caller's G [V][4][9] and su(3) force [V][4][8],
+// and the caller's momenta [V][4][8], which take P -= dt F.
+struct MdOut {
+  double2* g_int = nullptr;
+  double2* g_user = nullptr;
+  double* f_user = nullptr;
+  double* p_user = nullptr;
+  double dt = 0.0;
+};
+// Partial sums of the Wilson action's sum_{mu<nu} (1 - Re tr / 3) that a
+// gauge-force pass and launch_plaquette leave.
+int md_link_partials(const Geom& g);
+hipError_t launch_force_hop(const Geom& g, SpF64 ell_e, SpF64 ell_o, SpF64 rho_e, SpF64 rho_o, double coef,
+                            double2* gint, hipStream_t s);
+// Xi: [par][6][4][stride] double2.  ell_e.p == nullptr drops the fermion term;
+// cinv == nullptr the determinant term
+constexpr int kXiChunks = 4;
 hipError_t launch_clover_xi(const Geom& g, SpF64 ell_e, SpF64 ell_o, SpF64 rho_e, SpF64 rho_o, double w_e,
                             double w_o, const double2* cinv, double w_det, double2* xi, hipStream_t s);
-// coef_g != 0 adds the Wilson gauge force (weight coef_g, as launch_gauge_force) in the same pass
-hipError_t launch_force_clover(const Geom& g, const double2* u18, const double2* xi, double coef, double2* gint,
-                               hipStream_t s, double coef_g = 0.0);
-hipError_t launch_force_out(const Geom& g, const double2* u18, const double2* gint, double2* g_user,
-                            double* f_user, hipStream_t s);
-hipError_t launch_gauge_force(const Geom& g, const double2* u18, double coef, int accumulate, double2* gint,
-                              hipStream_t s);
-hipError_t launch_plaquette(const Geom& g, const double2* u18, double* partial, int block, hipStream_t s);
+// The force passes start from the accumulator gin (null: zero).  coef_g != 0
+// adds the Wilson gauge force (weight coef_g, as launch_gauge_force) in the
+// clover pass; partial (may be null) then receives the action's partial sums.
+hipError_t launch_force_clover(const Geom& g, const double2* u18, const double2* xi, double coef, double coef_g,
+                               const double2* gin, const MdOut& o, double* partial, hipStream_t s);
+hipError_t launch_gauge_force(const Geom& g, const double2* u18, double coef, const double2* gin, const MdOut& o,
+                              double* partial, hipStream_t s);
+hipError_t launch_force_finish(const Geom& g, const double2* u18, const double2* gin, const MdOut& o, hipStream_t s);
+hipError_t launch_plaquette(const Geom& g, const double2* u18, double* partial, hipStream_t s);
 hipError_t launch_sum_cb(const Geom& g, const double* v, double* partial, int block, hipStream_t s);
-hipError_t launch_force_zero(const Geom& g, double2* gint, hipStream_t s);
 hipError_t launch_reunitarize(const Geom& g, double2* u18, hipStream_t s);
 hipError_t launch_link_exp(const Geom& g, double2* u18, const double* p_user, double c, hipStream_t s);
-hipError_t launch_mom_update(const Geom& g, double* p_user, const double* f_user, double dt, hipStream_t s);
 
 }  // namespace qcd
