@@ -52,6 +52,8 @@ enum Slot { V_IN_E, V_IN_O, V_OUT_E, V_OUT_O, V_T, V_Q, V_X, V_R, V_P, V_RHS, V_
 enum HSlot { H_P, H_T, H_Q, H_R, H_IN, H_OUT, H_P1, H_P2, H_P3, NHSLOT };
 // ring of mailbox slots / events for the iterations in flight
 constexpr int kRing = 64;
+// steps of a trajectory whose actions wait in host-mapped memory
+constexpr int kActRing = 64;
 
 }  // namespace
 
@@ -123,6 +125,18 @@ struct qcd_ctx {
   double2* gint = nullptr;     // force accumulator: [mu][par][9][stride]
   double* md_partial = nullptr;  // partial sums of the molecular-dynamics kernels, then their span sums
   double* logdet = nullptr;    // ln det A(x) per odd site, from the last clover inversion
+  double* act_host = nullptr;  // host-mapped sums of the actions, [kActRing][3]: fermion, gauge, ln det
+  double* act_dev = nullptr;   // its device address
+
+  // the derived link copies that a call needs next (all: what the context keeps between calls)
+  LinkCopies copies(bool f64, bool half, bool half18) const {
+    LinkCopies l;
+    if (f64) l.u12 = u12;
+    if (half) l.uh = uh;
+    if (half18) l.uh18 = uh18;
+    return l;
+  }
+  LinkCopies all_copies() const { return copies(true, true, true); }
 
   // Workgroup size of the stencils and reductions, measured: 64 threads for
   // single-source work; 256 for the multi-source set, where FP64 solves are
@@ -254,6 +268,7 @@ void free_ctx(qcd_ctx* c) {
   f(c->md_partial);
   f(c->logdet);
   if (c->status_host) (void)hipHostFree(c->status_host);
+  if (c->act_host) (void)hipHostFree(c->act_host);
   for (auto& row : c->iter_graph)
     for (auto& gx : row)
       if (gx) (void)hipGraphExecDestroy(gx);
@@ -879,6 +894,10 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   if (rc == QCD_OK) rc = alloc_work(g, c->w1, 0, true);
   if (rc == QCD_OK && hipHostMalloc((void**)&c->status_host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess)
     rc = fail(QCD_ENOMEM, "pinned host allocation failed");
+  if (rc == QCD_OK && (hipHostMalloc((void**)&c->act_host, 3 * kActRing * sizeof(double),
+                                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+                       hipHostGetDevicePointer((void**)&c->act_dev, c->act_host, 0) != hipSuccess))
+    rc = fail(QCD_ENOMEM, "pinned host allocation failed");
   for (int k = 0; k < kRing && rc == QCD_OK; ++k)
     if (hipEventCreateWithFlags(&c->ev[k], hipEventDisableTiming) != hipSuccess) rc = fail(QCD_EHIP, "hipEventCreate failed");
   if (rc == QCD_OK && hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
@@ -960,8 +979,7 @@ int qcd_set_option(qcd_ctx* c, int option, int value) {
 int qcd_load_gauge(qcd_ctx* c, const void* U_dev) {
   QCHK(check_ctx(c));
   if (!U_dev) return fail(QCD_EINVAL, "null gauge pointer");
-  HIPCHK(launch_pack_gauge(c->g, (const double2*)U_dev, c->u18, c->stream));
-  HIPCHK(launch_derive_links(c->g, c->u18, c->u12, c->uh, c->uh18, c->stream));
+  HIPCHK(launch_pack_gauge(c->g, (const double2*)U_dev, c->u18, c->all_copies(), c->stream));
   c->gauge_loaded = true;
   c->clover_ready = false;
   return QCD_OK;
@@ -1219,8 +1237,9 @@ static int ensure_force_buffers(qcd_ctx* c) {
 // The fermion part of the force enters with weight wf; with det the
 // derivative of -2 sum_odd ln det A, also weighted wf, joins the clover part,
 // and with gauge_coef != 0 the Wilson gauge force, whose action's partial sums
-// then go to md_partial.  The last pass puts G where `out` says.
-static int force_core(qcd_ctx* c, const qcd_solver_params* p, double* S, CgCounters& cnt, int* conv_rc,
+// then go to md_partial.  The last pass puts G where `out` says.  The fermion
+// action goes to act_host[3 slot]; nothing waits for it here.
+static int force_core(qcd_ctx* c, const qcd_solver_params* p, int slot, CgCounters& cnt, int* conv_rc,
                       const MdOut& out, double wf = 1.0, bool det = false, double gauge_coef = 0.0) {
   const Geom& g = c->g;
   const int nb = nblocks(c);
@@ -1229,13 +1248,9 @@ static int force_core(qcd_ctx* c, const qcd_solver_params* p, double* S, CgCount
   int rc = run_cg(c, p, cnt);
   if (rc != QCD_OK) return rc;
   *conv_rc = c->w->st_host->rr_hi <= c->w->st_host->stop2 ? QCD_OK : QCD_ENOCONV;
-  CgState s_end = *c->w->st_host;
   // S = Re phi^dag X
   HIPCHK(launch_dot_re(c->w->gv, c->w->lg, c->f64(V_RHS), c->f64(V_X), c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nb, c->w->nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  if (S) *S = c->w->st_host->scalar;
-  *c->w->st_host = s_end;
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot, c->w->partial, nb, fold_area(c), c->stream));
   // Z = A_oo^{-1} H_oe X; Y = Mhat X; W = A_oo^{-1} g5 H_oe g5 Y
   QCHK(k1_f64(c, V_X, V_Z, false, nullptr));
   QCHK(k2_f64(c, V_X, V_Z, V_Y, false, 0, 0, 0.0, false, nullptr));
@@ -1277,13 +1292,46 @@ int qcd_action_force(qcd_ctx* c, const qcd_solver_params* p, const void* phi_dev
   MdOut out;
   out.g_user = (double2*)G_dev;
   out.f_user = F_dev;
-  QCHK(force_core(c, p, S, cnt, &conv, out));
+  QCHK(force_core(c, p, 0, cnt, &conv, out));
   if (X_dev) HIPCHK(launch_unpack_spinor_cb(c->g, c->f64(V_X), (double2*)X_dev, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  if (S) *S = c->act_host[0];
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   fill_stats(c, cnt, p, seconds, -1.0, stats);
   if (conv != QCD_OK) return fail(QCD_ENOCONV, "force solve reached max_iter without meeting tol");
   return QCD_OK;
+}
+
+// After a molecular-dynamics call that failed on its way: the links are those
+// it had reached, and every copy is brought in line with them.
+static int md_failed(qcd_ctx* c, int rc) {
+  if (c->gauge_loaded) (void)launch_derive_links(c->g, c->u18, c->all_copies(), c->stream);
+  return rc;
+}
+
+static int hmd_step_run(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* xi_dev,
+                        const qcd_solver_params* p, CgCounters& cnt, int* conv) {
+  const Geom& g = c->g;
+  QCHK(ensure_force_buffers(c));
+  // two flavours per pseudofermion at N_f = 2: the R algorithm draws the
+  // noise at the start of the step, phi = Mhat^dag(U_0) xi
+  HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, c->copies(true, false, false), c->stream));
+  c->gauge_loaded = true;
+  QCHK(qcd_build_clover(c));
+  HIPCHK(launch_pack_spinor_cb(g, (const double2*)xi_dev, c->f64(V_IN_E), c->stream));
+  QCHK(k1_f64(c, V_IN_E, V_T, true, nullptr));
+  QCHK(k2_f64(c, V_IN_E, V_T, V_RHS, true, 0, 0, 0.0, false, nullptr));
+  // U_1/2 = exp(i dt/2 P) U_0, where the force is taken
+  HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, false, false, c->copies(true, p->prec == QCD_MIXED, false), c->stream));
+  QCHK(qcd_build_clover(c));
+  // P <- P - dt F;  U <- exp(i dt/2 P) U_1/2
+  MdOut out;
+  out.p_user = P_dev;
+  out.dt = dt;
+  QCHK(force_core(c, p, 0, cnt, conv, out));
+  HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, false, false, c->all_copies(), c->stream));
+  HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
+  return qcd_build_clover(c);
 }
 
 int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* xi_dev,
@@ -1293,54 +1341,28 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
   if (!U_dev || !P_dev || !xi_dev) return fail(QCD_EINVAL, "null pointer");
   if (!std::isfinite(dt)) return fail(QCD_EINVAL, "dt must be finite");
   const auto t0 = std::chrono::steady_clock::now();
-  const Geom& g = c->g;
-  QCHK(ensure_force_buffers(c));
-  // two flavours per pseudofermion at N_f = 2: the R algorithm draws the
-  // noise at the start of the step, phi = Mhat^dag(U_0) xi
-  HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, c->stream));
-  HIPCHK(launch_derive_links(g, c->u18, c->u12, c->uh, c->uh18, c->stream));
-  c->gauge_loaded = true;
-  QCHK(qcd_build_clover(c));
-  HIPCHK(launch_pack_spinor_cb(g, (const double2*)xi_dev, c->f64(V_IN_E), c->stream));
-  QCHK(k1_f64(c, V_IN_E, V_T, true, nullptr));
-  QCHK(k2_f64(c, V_IN_E, V_T, V_RHS, true, 0, 0, 0.0, false, nullptr));
-  // U_1/2 = exp(i dt/2 P) U_0, where the force is taken
-  HIPCHK(launch_link_exp(g, c->u18, P_dev, 0.5 * dt, c->stream));
-  HIPCHK(launch_derive_links(g, c->u18, c->u12, c->uh, c->uh18, c->stream));
-  QCHK(qcd_build_clover(c));
   CgCounters cnt;
   int conv = QCD_OK;
-  // P <- P - dt F;  U <- exp(i dt/2 P) U_1/2
-  MdOut out;
-  out.p_user = P_dev;
-  out.dt = dt;
-  QCHK(force_core(c, p, S, cnt, &conv, out));
-  HIPCHK(launch_link_exp(g, c->u18, P_dev, 0.5 * dt, c->stream));
-  HIPCHK(launch_derive_links(g, c->u18, c->u12, c->uh, c->uh18, c->stream));
-  HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
-  QCHK(qcd_build_clover(c));
+  const int rc = hmd_step_run(c, dt, U_dev, P_dev, xi_dev, p, cnt, &conv);
+  if (rc != QCD_OK) return md_failed(c, rc);
+  if (S) *S = c->act_host[0];  // the clover build waited for the stream
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   fill_stats(c, cnt, p, seconds, -1.0, stats);
   if (conv != QCD_OK) return fail(QCD_ENOCONV, "force solve reached max_iter without meeting tol");
   return QCD_OK;
 }
 
-// beta times the sum of the partial sums of (1 - Re tr P / 3) in md_partial
-// (synchronises; overwrites the host state mirror)
-static int gauge_action_sync(qcd_ctx* c, double beta, double* S) {
+// The sum of the partial sums of (1 - Re tr P / 3) in md_partial to act_host[3 slot + 1]
+static int post_gauge_action(qcd_ctx* c, int slot) {
   const int n = md_link_partials(c->g);
-  HIPCHK(launch_fin_scalar(c->w->st, c->md_partial, n, 1, c->md_partial + n, c->stream));
-  QCHK(sync_state(c));
-  *S = beta * c->w->st_host->scalar;
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 1, c->md_partial, n, c->md_partial + n, c->stream));
   return QCD_OK;
 }
 
-// -2 sum_odd ln det A from the last inversion (synchronises)
-static int det_action_sync(qcd_ctx* c, double* S) {
+// sum_odd ln det A from the last inversion to act_host[3 slot + 2]
+static int post_logdet(qcd_ctx* c, int slot) {
   HIPCHK(launch_sum_cb(c->g, c->logdet, c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  *S = -2.0 * c->w->st_host->scalar;
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 2, c->w->partial, nblocks(c), fold_area(c), c->stream));
   return QCD_OK;
 }
 
@@ -1357,8 +1379,9 @@ int qcd_gauge_action_force(qcd_ctx* c, double beta, double* S, void* G_dev, doub
   } else if (S) {
     HIPCHK(launch_plaquette(c->g, c->u18, c->md_partial, c->stream));
   }
-  if (S) return gauge_action_sync(c, beta, S);
+  if (S) QCHK(post_gauge_action(c, 0));
   HIPCHK(hipStreamSynchronize(c->stream));
+  if (S) *S = beta * c->act_host[1];
   return QCD_OK;
 }
 
@@ -1381,7 +1404,7 @@ int qcd_clover_det_action_force(qcd_ctx* c, double* S, void* G_dev, double* F_de
   QCHK(check_ctx(c));
   QCHK(need_clover(c));
   QCHK(ensure_force_buffers(c));
-  if (S) QCHK(det_action_sync(c, S));
+  if (S) QCHK(post_logdet(c, 0));
   if (G_dev || F_dev) {
     const Geom& g = c->g;
     MdOut out;
@@ -1396,16 +1419,83 @@ int qcd_clover_det_action_force(qcd_ctx* c, double* S, void* G_dev, double* F_de
     }
   }
   HIPCHK(hipStreamSynchronize(c->stream));
+  if (S) *S = -2.0 * c->act_host[2];
   return QCD_OK;
 }
 
-// U <- exp(i h P) U on the packed links (h = 0 leaves them untouched)
-static int move_links(qcd_ctx* c, const double* P_dev, double h, bool reunit) {
-  if (h != 0.0) HIPCHK(launch_link_exp(c->g, c->u18, P_dev, h, c->stream));
-  if (reunit) HIPCHK(launch_reunitarize(c->g, c->u18, c->stream));
-  HIPCHK(launch_derive_links(c->g, c->u18, c->u12, c->uh, c->uh18, c->stream));
+// The steps of qcd_md_trajectory.
+static int md_run(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* P_dev, const void* xi_dev,
+                  const qcd_solver_params* p, double* actions, CgCounters& cnt, int* conv_all) {
+  const Geom& g = c->g;
+  const double dt = md->dt, wf = 0.5 * md->n_f;
+  const bool ferm = wf != 0.0, det = md->clover_det == 1 && ferm, reunit = md->reunitarize == 1;
+  // R algorithm (Gottlieb et al. 1987): the noise is drawn (n_f/2) dt/2
+  // before the force point, at U(t + (1 - n_f/2) dt/2); at n_f = 2 that
+  // is the start of the step, and for n_f > 2 the links first move back
+  const double h1 = (1.0 - wf) * 0.5 * dt;
+  // Link copies: of the links where the noise is drawn the FP64 one, at the
+  // force point what the solver reads, at the end all; none between the
+  // moves of a pure-gauge step.  A pure-gauge step's last move and the next
+  // one's first are by the same momenta and go in one pass.
+  const LinkCopies draw_copies = c->copies(ferm, false, false);
+  const LinkCopies solve_copies = c->copies(ferm, ferm && p->prec == QCD_MIXED, false);
+  if (ferm) QCHK(ensure_force_buffers(c));
+  HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, draw_copies, c->stream));
   c->gauge_loaded = true;
   c->clover_ready = false;
+  if (!ferm) HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, false, false, LinkCopies{}, c->stream));
+  int first = 0;  // the step in slot 0 of act_host
+  for (int k = 0; k < md->n_steps; ++k) {
+    const bool last = k == md->n_steps - 1;
+    const int slot = k - first;
+    c->act_host[3 * slot] = c->act_host[3 * slot + 1] = c->act_host[3 * slot + 2] = 0.0;
+    if (ferm) {
+      if (h1 != 0.0) HIPCHK(launch_move_links(g, c->u18, P_dev, h1, false, false, draw_copies, c->stream));
+      QCHK(qcd_build_clover(c));
+      const double2* xi_k = (const double2*)xi_dev + (size_t)k * g.Vh * 12;
+      HIPCHK(launch_pack_spinor_cb(g, xi_k, c->f64(V_IN_E), c->stream));
+      QCHK(k1_f64(c, V_IN_E, V_T, true, nullptr));
+      QCHK(k2_f64(c, V_IN_E, V_T, V_RHS, true, 0, 0, 0.0, false, nullptr));
+      HIPCHK(launch_move_links(g, c->u18, P_dev, wf * 0.5 * dt, false, false, solve_copies, c->stream));
+      c->clover_ready = false;
+      QCHK(qcd_build_clover(c));
+    }
+    if (det && actions) QCHK(post_logdet(c, slot));
+    // P <- P - dt F in the last force pass; the gauge force joins it, and
+    // leaves the gauge action's partial sums
+    const double gauge_coef = md->beta != 0.0 ? -md->beta / 3.0 : 0.0;
+    MdOut out;
+    out.p_user = P_dev;
+    out.dt = dt;
+    if (ferm) {
+      int conv = QCD_OK;
+      QCHK(force_core(c, p, slot, cnt, &conv, out, wf, det, gauge_coef));
+      if (conv != QCD_OK) *conv_all = conv;
+    } else if (gauge_coef != 0.0) {
+      HIPCHK(launch_gauge_force(g, c->u18, gauge_coef, nullptr, out, actions ? c->md_partial : nullptr, c->stream));
+    } else {
+      HIPCHK(launch_force_finish(g, c->u18, nullptr, out, c->stream));
+    }
+    if (gauge_coef != 0.0 && actions) QCHK(post_gauge_action(c, slot));
+    const LinkCopies end_copies = last ? c->all_copies() : (h1 == 0.0 ? draw_copies : LinkCopies{});
+    HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, reunit, !ferm && !last, end_copies, c->stream));
+    c->clover_ready = false;
+    if (actions && (last || slot == kActRing - 1)) {
+      HIPCHK(hipStreamSynchronize(c->stream));
+      for (int j = first; j <= k; ++j) {
+        const double* a = c->act_host + 3 * (j - first);
+        actions[3 * j] = a[0];
+        actions[3 * j + 1] = md->beta * a[1];
+        actions[3 * j + 2] = -2.0 * a[2];
+      }
+      first = k + 1;
+    } else if (slot == kActRing - 1) {
+      first = k + 1;
+    }
+  }
+  HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
+  if (ferm) QCHK(qcd_build_clover(c));
+  HIPCHK(hipStreamSynchronize(c->stream));
   return QCD_OK;
 }
 
@@ -1419,65 +1509,16 @@ int qcd_md_trajectory(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* 
     return fail(QCD_EINVAL, "dt, beta must be finite and n_f finite and >= 0");
   if ((md->clover_det != 0 && md->clover_det != 1) || (md->reunitarize != 0 && md->reunitarize != 1))
     return fail(QCD_EINVAL, "clover_det and reunitarize must be 0 or 1");
-  const double wf = 0.5 * md->n_f;
-  const bool ferm = wf != 0.0, det = md->clover_det == 1 && wf != 0.0;
+  const bool ferm = 0.5 * md->n_f != 0.0;
   if (ferm) {
     QCHK(validate_params(p));
     if (!xi_dev) return fail(QCD_EINVAL, "null noise pointer");
   }
   const auto t0 = std::chrono::steady_clock::now();
-  const Geom& g = c->g;
-  const double dt = md->dt;
-  if (ferm) QCHK(ensure_force_buffers(c));
-  HIPCHK(launch_pack_gauge(g, (const double2*)U_dev, c->u18, c->stream));
-  QCHK(move_links(c, P_dev, 0.0, false));  // the derived link copies of U_0
   CgCounters cnt;
   int conv_all = QCD_OK;
-  for (int k = 0; k < md->n_steps; ++k) {
-    double s_f = 0.0, s_g = 0.0, s_d = 0.0;
-    if (ferm) {
-      // R algorithm (Gottlieb et al. 1987): the noise is drawn (n_f/2) dt/2
-      // before the force point, at U(t + (1 - n_f/2) dt/2); at n_f = 2 that
-      // is the start of the step, and for n_f > 2 the links first move back
-      const double h1 = (1.0 - wf) * 0.5 * dt;
-      if (h1 != 0.0) QCHK(move_links(c, P_dev, h1, false));
-      QCHK(qcd_build_clover(c));
-      const double2* xi_k = (const double2*)xi_dev + (size_t)k * g.Vh * 12;
-      HIPCHK(launch_pack_spinor_cb(g, xi_k, c->f64(V_IN_E), c->stream));
-      QCHK(k1_f64(c, V_IN_E, V_T, true, nullptr));
-      QCHK(k2_f64(c, V_IN_E, V_T, V_RHS, true, 0, 0, 0.0, false, nullptr));
-      QCHK(move_links(c, P_dev, wf * 0.5 * dt, false));
-      QCHK(qcd_build_clover(c));
-    } else {
-      QCHK(move_links(c, P_dev, 0.5 * dt, false));
-    }
-    if (det) QCHK(det_action_sync(c, &s_d));
-    // P <- P - dt F in the last force pass; the gauge force joins it, and
-    // leaves the gauge action's partial sums
-    const double gauge_coef = md->beta != 0.0 ? -md->beta / 3.0 : 0.0;
-    MdOut out;
-    out.p_user = P_dev;
-    out.dt = dt;
-    if (ferm) {
-      int conv = QCD_OK;
-      QCHK(force_core(c, p, &s_f, cnt, &conv, out, wf, det, gauge_coef));
-      if (conv != QCD_OK) conv_all = conv;
-    } else if (gauge_coef != 0.0) {
-      HIPCHK(launch_gauge_force(g, c->u18, gauge_coef, nullptr, out, c->md_partial, c->stream));
-    } else {
-      HIPCHK(launch_force_finish(g, c->u18, nullptr, out, c->stream));
-    }
-    if (md->beta != 0.0 && actions) QCHK(gauge_action_sync(c, md->beta, &s_g));
-    QCHK(move_links(c, P_dev, 0.5 * dt, md->reunitarize == 1));
-    if (actions) {
-      actions[3 * k] = s_f;
-      actions[3 * k + 1] = s_g;
-      actions[3 * k + 2] = s_d;
-    }
-  }
-  HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
-  if (ferm) QCHK(qcd_build_clover(c));
-  HIPCHK(hipStreamSynchronize(c->stream));
+  const int rc = md_run(c, md, U_dev, P_dev, xi_dev, p, actions, cnt, &conv_all);
+  if (rc != QCD_OK) return md_failed(c, rc);
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   if (stats) {
     if (ferm) {

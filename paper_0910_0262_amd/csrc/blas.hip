@@ -7,7 +7,7 @@
 // derive alpha, beta and the stopping / reliable-update decisions.
 #include <type_traits>
 
-#include "qcd_internal.h"
+#include "links.h"
 
 namespace qcd {
 
@@ -119,86 +119,56 @@ hipError_t launch_unpack_spinor_cb(const Geom& g, SpF64 f, double2* user, hipStr
 }
 
 // ------------------------------------------------------------------ gauge packing
-// user: complex128 [V][4][3][3]; u18: double2 [(mu*2 + par)*9 + k][stride]
-__global__ void pack_gauge_k(Geom g, const double2* __restrict__ user, double2* __restrict__ u18) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 4 * g.V) return;
-  const int i = t >> 2, mu = t & 3;
-  int x[4];
-  lex_coords(i, g, x);
-  const int par = parity_of(x), cb = i >> 1;
-  double2* dst = u18 + (size_t)((mu * 2 + par) * 9) * g.stride + cb;
+// user: complex128 [V][4][3][3]; u18: double2 [(mu*2 + par)*9 + k][stride].
+// Packing also writes the derived copies, which had a pass of their own over
+// the packed links; a work-item read or wrote its link's 144 bytes itself, 16
+// at a time and 576 apart (at 32^3x64 0.57 + 0.54 ms for pack and copies and
+// 0.69 ms for unpack; load of a configuration 1.10 -> 0.73 ms, 5 TB/s).
+__global__ void __launch_bounds__(256) pack_gauge_k(Geom g, const double2* __restrict__ user, double2* __restrict__ u18,
+                                                    LinkCopies c) {
+  __shared__ TileLds<9> lds;
+  tile_read<9>(lds, g, user);
+  const TileLink t = tile_link(g);
+  if (!t.live) return;
+  const int q = t.mu * 2 + t.par;
+  double2 r[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) dst[(size_t)k * g.stride] = user[(size_t)t * 9 + k];
-}
-__global__ void unpack_gauge_k(Geom g, const double2* __restrict__ u18, double2* __restrict__ user) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 4 * g.V) return;
-  const int i = t >> 2, mu = t & 3;
-  int x[4];
-  lex_coords(i, g, x);
-  const int par = parity_of(x), cb = i >> 1;
-  const double2* src = u18 + (size_t)((mu * 2 + par) * 9) * g.stride + cb;
+  for (int k = 0; k < 9; ++k) r[k] = lds.at(t, k);
 #pragma unroll
-  for (int k = 0; k < 9; ++k) user[(size_t)t * 9 + k] = src[(size_t)k * g.stride];
+  for (int k = 0; k < 9; ++k) u18[(size_t)(q * 9 + k) * g.stride + t.cb] = r[k];
+  store_copies(c, g.stride, q, t.cb, r);
 }
-// FP64 12-real (first two rows) and binary16 12-real copies of the links.
-// binary16 entries are rounded float64 -> float32 -> binary16, both to nearest even.
-__global__ void derive_links_k(Geom g, const double2* __restrict__ u18, double2* __restrict__ u12,
-                               uint2* __restrict__ uh, uint4* __restrict__ uh18) {
+__global__ void __launch_bounds__(256) unpack_gauge_k(Geom g, const double2* __restrict__ u18, double2* __restrict__ user) {
+  __shared__ TileLds<9> lds;
+  const TileLink t = tile_link(g);
+  if (t.live) {
+    const int q = t.mu * 2 + t.par;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) lds.at(t, k) = u18[(size_t)(q * 9 + k) * g.stride + t.cb];
+  }
+  tile_write<9>(lds, g, user);
+}
+// The copies alone, from the packed links.
+__global__ void derive_links_k(Geom g, const double2* __restrict__ u18, LinkCopies c) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= 8 * g.Vh) return;
   const int q = t / g.Vh, cb = t - q * g.Vh;  // q = mu * 2 + par
-  const double2* src = u18 + (size_t)(q * 9) * g.stride + cb;
   double2 r[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) r[k] = src[(size_t)k * g.stride];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) u12[(size_t)(q * 6 + k) * g.stride + cb] = r[k];
-  {  // rows 0, 1: halves 0-7 in a 16-byte chunk, 8-11 in an 8-byte one
-    h8_t a;
-    h4_t b;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      a[2 * k] = (_Float16)(float)r[k].x;
-      a[2 * k + 1] = (_Float16)(float)r[k].y;
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      b[2 * k] = (_Float16)(float)r[4 + k].x;
-      b[2 * k + 1] = (_Float16)(float)r[4 + k].y;
-    }
-    uint4* p4 = (uint4*)uh;
-    p4[(size_t)q * g.stride + cb] = from_h8(a);
-    ((uint2*)(p4 + (size_t)8 * g.stride))[(size_t)q * g.stride + cb] = from_h4(b);
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    h8_t h;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      h[2 * j] = (_Float16)(float)r[4 * k + j].x;
-      h[2 * j + 1] = (_Float16)(float)r[4 * k + j].y;
-    }
-    uh18[(size_t)(q * 2 + k) * g.stride + cb] = from_h8(h);
-  }
-  h2_t h;
-  h[0] = (_Float16)(float)r[8].x;
-  h[1] = (_Float16)(float)r[8].y;
-  ((unsigned int*)(uh18 + (size_t)16 * g.stride))[(size_t)q * g.stride + cb] = from_h2(h);
+  for (int k = 0; k < 9; ++k) r[k] = u18[(size_t)(q * 9 + k) * g.stride + cb];
+  store_copies(c, g.stride, q, cb, r);
 }
 
-hipError_t launch_pack_gauge(const Geom& g, const double2* user, double2* u18, hipStream_t s) {
-  hipLaunchKernelGGL(pack_gauge_k, dim3(blocks_for(4 * g.V, 256)), dim3(256), 0, s, g, user, u18);
+hipError_t launch_pack_gauge(const Geom& g, const double2* user, double2* u18, const LinkCopies& c, hipStream_t s) {
+  hipLaunchKernelGGL(pack_gauge_k, dim3(tile_blocks(g)), dim3(256), 0, s, g, user, u18, c);
   return hipGetLastError();
 }
 hipError_t launch_unpack_gauge(const Geom& g, const double2* u18, double2* user, hipStream_t s) {
-  hipLaunchKernelGGL(unpack_gauge_k, dim3(blocks_for(4 * g.V, 256)), dim3(256), 0, s, g, u18, user);
+  hipLaunchKernelGGL(unpack_gauge_k, dim3(tile_blocks(g)), dim3(256), 0, s, g, u18, user);
   return hipGetLastError();
 }
-hipError_t launch_derive_links(const Geom& g, const double2* u18, double2* u12, uint2* uh, uint4* uh18,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(derive_links_k, dim3(blocks_for(8 * g.Vh, 256)), dim3(256), 0, s, g, u18, u12, uh, uh18);
+hipError_t launch_derive_links(const Geom& g, const double2* u18, const LinkCopies& c, hipStream_t s) {
+  hipLaunchKernelGGL(derive_links_k, dim3(blocks_for(8 * g.Vh, 256)), dim3(256), 0, s, g, u18, c);
   return hipGetLastError();
 }
 
@@ -300,6 +270,14 @@ __global__ void fin_scalar_k(CgState* st, const double* partial, int n) {
   partial += (size_t)blockIdx.x * n;
   const double s = block_sum_partials(partial, n);
   if (threadIdx.x == 0) st->scalar = s;
+}
+// The sum into host-mapped memory, for the host to read once the stream has been waited for.
+__global__ void fin_sum_k(double* out, const double* partial, int n) {
+  const double s = block_sum_partials(partial, n);
+  if (threadIdx.x == 0) {
+    *out = s;
+    __threadfence_system();
+  }
 }
 __global__ void fin_init_k(CgState* st, const double* partial, int n, double tol, double delta, int max_iter,
                            int mixed, CgState* mbox, int ring) {
@@ -406,6 +384,10 @@ __global__ void __launch_bounds__(256) fold_partials_k(const double* partial, in
 
 hipError_t launch_fin_scalar(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s) {
   FIN_LAUNCH(fin_scalar_k, st, partial, n)
+}
+hipError_t launch_fin_sum(double* out, const double* partial, int n, double* fold, hipStream_t s) {
+  const int nr = 1;
+  FIN_LAUNCH(fin_sum_k, out, partial, n)
 }
 hipError_t launch_fin_init(CgState* st, const double* partial, int n, int nr, double* fold, double tol, double delta,
                            int max_iter, int mixed, CgState* mbox, int ring, hipStream_t s) {

@@ -19,6 +19,7 @@
 // of the traceless part of Gamma; each link enters the leaves of 6 plaquettes
 // at 4 corners each, and a leaf derivative is the product of the other three
 // links with Xi inserted at the leaf's corner.
+#include "links.h"
 #include "md_order.h"
 
 namespace qcd {
@@ -650,18 +651,76 @@ hipError_t launch_sum_cb(const Geom& g, const double* v, double* partial, int bl
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ reunitarisation
-// Row 0 normalised, row 1 orthogonalised against it and normalised, row 2 =
-// conj(row 0 x row 1): the nearest SU(3) matrix in the Gram-Schmidt sense.
-__global__ void __launch_bounds__(128) reunitarize_k(Geom g, double2* __restrict__ u18) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 4 * g.V) return;
-  const int mu = t / g.V, i = t - mu * g.V;
-  int x[4];
-  lex_coords(i, g, x);
-  const int par = parity_of(x), cb = i >> 1;
-  double2* base = u18 + (size_t)((mu * 2 + par) * 9) * g.stride;
-  Mat<double> u = load_mat(base, g.stride, cb);
+// ------------------------------------------------------------------ HMD updates
+// f_j of exp(iQ) = f0 + f1 Q + f2 Q^2 in closed form (c1 > 0)
+__device__ void expi_closed(double c0, double c1, Cx<double>& f0, Cx<double>& f1, Cx<double>& f2) {
+  const bool neg = c0 < 0.0;
+  const double c0a = fabs(c0);
+  const double c0max = 2.0 * pow(c1 / 3.0, 1.5);
+  double ratio = c0a / c0max;
+  ratio = ratio > 1.0 ? 1.0 : ratio;
+  const double theta = acos(ratio);
+  const double u = sqrt(c1 / 3.0) * cos(theta / 3.0);
+  const double w = sqrt(c1) * sin(theta / 3.0);
+  const double u2 = u * u, w2 = w * w;
+  const double xi0 = fabs(w) < 0.05 ? 1.0 - w2 / 6.0 * (1.0 - w2 / 20.0 * (1.0 - w2 / 42.0)) : sin(w) / w;
+  const double cw = cos(w);
+  const Cx<double> e2iu = {cos(2.0 * u), sin(2.0 * u)}, emiu = {cos(u), -sin(u)};
+  Cx<double> h0 = (u2 - w2) * e2iu + emiu * Cx<double>{8.0 * u2 * cw, 2.0 * u * (3.0 * u2 + w2) * xi0};
+  Cx<double> h1 = (2.0 * u) * e2iu - emiu * Cx<double>{2.0 * u * cw, -(3.0 * u2 - w2) * xi0};
+  Cx<double> h2 = e2iu - emiu * Cx<double>{cw, 3.0 * u * xi0};
+  const double den = 1.0 / (9.0 * u2 - w2);
+  f0 = den * h0;
+  f1 = den * h1;
+  f2 = den * h2;
+  if (neg) {  // f_j(-c0) = (-1)^j conj(f_j(c0))
+    f0 = conj(f0);
+    f1 = -conj(f1);
+    f2 = conj(f2);
+  }
+}
+// exp(i Q) = f0 + f1 Q + f2 Q^2 for Hermitian traceless Q, with f_j from
+// c0 = det Q = tr(Q^3)/3 and c1 = tr(Q^2)/2 (Cayley-Hamilton: Q^3 = c1 Q + c0).
+// For |Q| <= 1/2 (the eigenvalues are at most 2 sqrt(c1/3)) the power series
+// to order 15, whose remainder is below 1e-18, by Horner's rule on the three
+// coefficients: a step of the integrator is far inside, and the closed form's
+// arc cosine, power and six sines and cosines were most of what a link's
+// update computed.  Beyond, the closed form of Morningstar and Peardon (Phys.
+// Rev. D 69 (2004) 054501).
+__device__ Mat<double> expi_herm(const Mat<double>& q) {
+  const Mat<double> q2 = mm(q, q);
+  const double c1 = 0.5 * (q2.m[0][0].re + q2.m[1][1].re + q2.m[2][2].re);
+  Mat<double> out;
+  const Mat<double> q3 = mm(q2, q);
+  const double c0 = (q3.m[0][0].re + q3.m[1][1].re + q3.m[2][2].re) / 3.0;
+  Cx<double> f0, f1, f2;
+  if (c1 <= 0.1875) {
+    f0 = {1.0, 0.0};
+    f1 = f2 = {0.0, 0.0};
+#pragma unroll
+    for (int k = 15; k >= 1; --k) {  // f <- 1 + (i Q / k) f
+      const double w = 1.0 / k;
+      const Cx<double> t0 = c0 * f2, t1 = axpy(f0, c1, f2);
+      f2 = w * ti(f1);
+      f1 = w * ti(t1);
+      f0 = {1.0 - w * t0.im, w * t0.re};
+    }
+  } else {
+    expi_closed(c0, c1, f0, f1, f2);
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      out.m[a][b] = f1 * q.m[a][b] + f2 * q2.m[a][b];
+      if (a == b) out.m[a][b] = out.m[a][b] + f0;
+    }
+  return out;
+}
+
+// Back to SU(3): row 0 normalised, row 1 orthogonalised against it and
+// normalised, row 2 = conj(row 0 x row 1).
+__device__ __forceinline__ void reunitarize(Mat<double>& u) {
   double n0 = 0.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) n0 += norm2(u.m[0][c]);
@@ -683,96 +742,62 @@ __global__ void __launch_bounds__(128) reunitarize_k(Geom g, double2* __restrict
   u.m[2][0] = conj(u.m[0][1] * u.m[1][2] - u.m[0][2] * u.m[1][1]);
   u.m[2][1] = conj(u.m[0][2] * u.m[1][0] - u.m[0][0] * u.m[1][2]);
   u.m[2][2] = conj(u.m[0][0] * u.m[1][1] - u.m[0][1] * u.m[1][0]);
-  store_mat(base, g.stride, cb, u);
 }
 
-hipError_t launch_reunitarize(const Geom& g, double2* u18, hipStream_t s) {
-  hipLaunchKernelGGL(reunitarize_k, dim3(blocks_for(4 * g.V, 128)), dim3(128), 0, s, g, u18);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ HMD updates
-// exp(i Q) for Hermitian traceless Q by the Cayley-Hamilton form of
-// Morningstar and Peardon (Phys. Rev. D 69 (2004) 054501):
-// exp(iQ) = f0 + f1 Q + f2 Q^2 with f_j from c0 = det Q, c1 = tr(Q^2)/2.
-__device__ Mat<double> expi_herm(const Mat<double>& q) {
-  const Mat<double> q2 = mm(q, q);
-  const double c1 = 0.5 * (q2.m[0][0].re + q2.m[1][1].re + q2.m[2][2].re);
-  Mat<double> out;
-  if (c1 < 1e-36) {  // exp(iQ) = 1 + iQ - Q^2 / 2 + O(|Q|^3)
+// U <- E U with E = exp(i h P), P = sum_a P^a lambda^a / 2; reunitarisation; E
+// once more (the end of a step and the start of the next move the links by the
+// same momenta); the copies.  Bound by the bytes of U, P and the copies, so
+// all of it is one pass: exponential, reunitarisation and copies as three
+// passes took 0.66 + 0.40 + 0.55 ms at 32^3x64 and, twice in a pure-gauge step
+// of 142 us at 16^4, 77 us (the step now 77 us in all).
+__global__ void __launch_bounds__(256) move_links_k(Geom g, double2* __restrict__ u18, const double* __restrict__ p_user,
+                                                    double h, int reunit, int twice, LinkCopies c) {
+  __shared__ TileLds<4> lds;
+  if (h != 0.0) tile_read<4>(lds, g, (const d2_a8*)p_user);
+  const TileLink t = tile_link(g);
+  if (!t.live) return;
+  double2* const base = u18 + (size_t)((t.mu * 2 + t.par) * 9) * g.stride;
+  Mat<double> U = load_mat(base, g.stride, t.cb);
+  if (h != 0.0) {
+    double P[8];
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        out.m[a][b] = ti(q.m[a][b]) - 0.5 * q2.m[a][b];
-        if (a == b) out.m[a][b].re += 1.0;
-      }
-    return out;
-  }
-  const Mat<double> q3 = mm(q2, q);
-  const double c0 = (q3.m[0][0].re + q3.m[1][1].re + q3.m[2][2].re) / 3.0;
-  const bool neg = c0 < 0.0;
-  const double c0a = fabs(c0);
-  const double c0max = 2.0 * pow(c1 / 3.0, 1.5);
-  double ratio = c0a / c0max;
-  ratio = ratio > 1.0 ? 1.0 : ratio;
-  const double theta = acos(ratio);
-  const double u = sqrt(c1 / 3.0) * cos(theta / 3.0);
-  const double w = sqrt(c1) * sin(theta / 3.0);
-  const double u2 = u * u, w2 = w * w;
-  const double xi0 = fabs(w) < 0.05 ? 1.0 - w2 / 6.0 * (1.0 - w2 / 20.0 * (1.0 - w2 / 42.0)) : sin(w) / w;
-  const double cw = cos(w);
-  const Cx<double> e2iu = {cos(2.0 * u), sin(2.0 * u)}, emiu = {cos(u), -sin(u)};
-  Cx<double> h0 = (u2 - w2) * e2iu + emiu * Cx<double>{8.0 * u2 * cw, 2.0 * u * (3.0 * u2 + w2) * xi0};
-  Cx<double> h1 = (2.0 * u) * e2iu - emiu * Cx<double>{2.0 * u * cw, -(3.0 * u2 - w2) * xi0};
-  Cx<double> h2 = e2iu - emiu * Cx<double>{cw, 3.0 * u * xi0};
-  const double den = 1.0 / (9.0 * u2 - w2);
-  Cx<double> f0 = den * h0, f1 = den * h1, f2 = den * h2;
-  if (neg) {  // f_j(-c0) = (-1)^j conj(f_j(c0))
-    f0 = conj(f0);
-    f1 = -conj(f1);
-    f2 = conj(f2);
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      out.m[a][b] = f1 * q.m[a][b] + f2 * q2.m[a][b];
-      if (a == b) out.m[a][b] = out.m[a][b] + f0;
+    for (int k = 0; k < 4; ++k) {
+      const double2 d = lds.at(t, k);
+      P[2 * k] = 0.5 * h * d.x;
+      P[2 * k + 1] = 0.5 * h * d.y;
     }
-  return out;
-}
-
-// U_mu(x) <- exp(i c P_mu(x)) U_mu(x), P = sum_a P^a lambda^a / 2
-__global__ void __launch_bounds__(128) link_exp_k(Geom g, double2* __restrict__ u18, const double* __restrict__ p_user,
-                                                  double c) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 4 * g.V) return;
-  const int i = t >> 2, mu = t & 3;
-  int x[4];
-  lex_coords(i, g, x);
-  const int par = parity_of(x), cb = i >> 1;
-  double P[8];
+    const double r3 = 0.57735026918962576451;  // 1 / sqrt(3)
+    Mat<double> q;
+    q.m[0][0] = {P[2] + P[7] * r3, 0.0};
+    q.m[1][1] = {-P[2] + P[7] * r3, 0.0};
+    q.m[2][2] = {-2.0 * P[7] * r3, 0.0};
+    q.m[0][1] = {P[0], -P[1]};
+    q.m[1][0] = {P[0], P[1]};
+    q.m[0][2] = {P[3], -P[4]};
+    q.m[2][0] = {P[3], P[4]};
+    q.m[1][2] = {P[5], -P[6]};
+    q.m[2][1] = {P[5], P[6]};
+    const Mat<double> E = expi_herm(q);
+    U = mm(E, U);
+    if (reunit) reunitarize(U);
+    if (twice) U = mm(E, U);
+  } else if (reunit) {
+    reunitarize(U);
+  }
+  double2 r[9];
 #pragma unroll
-  for (int a = 0; a < 8; ++a) P[a] = 0.5 * c * p_user[(size_t)t * 8 + a];
-  const double r3 = 0.57735026918962576451;
-  Mat<double> q;
-  q.m[0][0] = {P[2] + P[7] * r3, 0.0};
-  q.m[1][1] = {-P[2] + P[7] * r3, 0.0};
-  q.m[2][2] = {-2.0 * P[7] * r3, 0.0};
-  q.m[0][1] = {P[0], -P[1]};
-  q.m[1][0] = {P[0], P[1]};
-  q.m[0][2] = {P[3], -P[4]};
-  q.m[2][0] = {P[3], P[4]};
-  q.m[1][2] = {P[5], -P[6]};
-  q.m[2][1] = {P[5], P[6]};
-  double2* base = u18 + (size_t)((mu * 2 + par) * 9) * g.stride;
-  const Mat<double> U = load_mat(base, g.stride, cb);
-  store_mat(base, g.stride, cb, mm(expi_herm(q), U));
+  for (int k = 0; k < 9; ++k) r[k] = make_double2(U.m[k / 3][k % 3].re, U.m[k / 3][k % 3].im);
+  if (h != 0.0 || reunit) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) base[(size_t)k * g.stride + t.cb] = r[k];
+  }
+  store_copies(c, g.stride, t.mu * 2 + t.par, t.cb, r);
 }
 
-hipError_t launch_link_exp(const Geom& g, double2* u18, const double* p_user, double c, hipStream_t s) {
-  hipLaunchKernelGGL(link_exp_k, dim3(blocks_for(4 * g.V, 128)), dim3(128), 0, s, g, u18, p_user, c);
+hipError_t launch_move_links(const Geom& g, double2* u18, const double* p_user, double h, bool reunit, bool twice,
+                             const LinkCopies& c, hipStream_t s) {
+  hipLaunchKernelGGL(move_links_k, dim3(tile_blocks(g)), dim3(256), 0, s, g, u18, p_user, h, reunit ? 1 : 0,
+                     twice ? 1 : 0, c);
   return hipGetLastError();
 }
 

@@ -164,12 +164,17 @@ hipError_t launch_unpack_spinor_cb(const Geom& g, SpF64 f, double2* user, hipStr
 hipError_t launch_pack_spinor_multi(const Geom& g, int lg, int n, const double2* user, SpF64 e, SpF64 o,
                                     hipStream_t s);
 hipError_t launch_unpack_spinor_multi(const Geom& g, int lg, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s);
-hipError_t launch_pack_gauge(const Geom& g, const double2* user, double2* u18, hipStream_t s);
+// Copies of the links the stencils read, any of them null where it is not
+// wanted.  u12: FP64 rows 0, 1; uh: binary16 rows 0, 1; uh18: all nine binary16
+// entries (16 * stride uint4 chunks followed by 8 * stride 32-bit chunks).
+struct LinkCopies {
+  double2* u12 = nullptr;
+  uint2* uh = nullptr;
+  uint4* uh18 = nullptr;
+};
+hipError_t launch_pack_gauge(const Geom& g, const double2* user, double2* u18, const LinkCopies& c, hipStream_t s);
 hipError_t launch_unpack_gauge(const Geom& g, const double2* u18, double2* user, hipStream_t s);
-// u12: FP64 rows 0, 1; uh: binary16 rows 0, 1; uh18: all nine binary16 entries
-// (16 * stride uint4 chunks followed by 8 * stride 32-bit chunks)
-hipError_t launch_derive_links(const Geom& g, const double2* u18, double2* u12, uint2* uh, uint4* uh18,
-                               hipStream_t s);
+hipError_t launch_derive_links(const Geom& g, const double2* u18, const LinkCopies& c, hipStream_t s);
 hipError_t launch_pack_clover(const Geom& g, const double2* user, double2* clov, hipStream_t s);
 hipError_t launch_unpack_clover(const Geom& g, const double2* clov, double2* user, int n_par, int par0,
                                 hipStream_t s);
@@ -186,6 +191,8 @@ hipError_t launch_dot_re(const Geom& gv, int lg, SpF64 a, SpF64 b, double* parti
 constexpr int kFoldSpan = 4096;
 constexpr int kFoldMin = 32768;
 hipError_t launch_fin_scalar(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s);
+// the sum of n partials of one right-hand side to *out (device or host-mapped memory)
+hipError_t launch_fin_sum(double* out, const double* partial, int n, double* fold, hipStream_t s);
 hipError_t launch_fin_init(CgState* st, const double* partial, int n, int nr, double* fold, double tol, double delta,
                            int max_iter, int mixed, CgState* mbox, int ring, hipStream_t s);
 hipError_t launch_fin_alpha(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s);
@@ -248,7 +255,9 @@ hipError_t launch_gauge_force(const Geom& g, const double2* u18, double coef, co
 hipError_t launch_force_finish(const Geom& g, const double2* u18, const double2* gin, const MdOut& o, hipStream_t s);
 hipError_t launch_plaquette(const Geom& g, const double2* u18, double* partial, hipStream_t s);
 hipError_t launch_sum_cb(const Geom& g, const double* v, double* partial, int block, hipStream_t s);
-hipError_t launch_reunitarize(const Geom& g, double2* u18, hipStream_t s);
-hipError_t launch_link_exp(const Geom& g, double2* u18, const double* p_user, double c, hipStream_t s);
+// U <- exp(i h P) U (h = 0: U as it is), then back to SU(3) where reunit is
+// set, then exp(i h P) U once more where twice is set; and the copies of the result
+hipError_t launch_move_links(const Geom& g, double2* u18, const double* p_user, double h, bool reunit, bool twice,
+                             const LinkCopies& c, hipStream_t s);
 
 }  // namespace qcd

@@ -75,3 +75,62 @@ def test_one_double_alignment(case):
         ends.append(uu)
     assert torch.equal(p, p1) and torch.equal(ends[0], ends[1])
     lat.load_gauge(to_dev(u))
+
+
+@pytest.mark.parametrize("scale", [0.01, 0.3, 0.42, 0.44, 3.0])
+def test_link_move(scale):
+    """A force-free trajectory is U -> exp(i dt P) U: the power series, the closed form, and both
+    sides of the line between them (c1 = 0.1875, which these momenta cross between 0.42 and 0.44)."""
+    dims = (2, 6, 4, 2)
+    u = torch.as_tensor(synth.random_su3_field(dims, 0.3, 5))
+    p = torch.as_tensor(synth.momenta(dims, 5))
+    p = p / p.norm(dim=-1, keepdim=True) * 4.0 * scale  # c1 = |h P|^2 / 4 = scale^2 with h = dt / 2 = 0.5
+    lat = Lattice(dims, KAPPA, CSW)
+    ud, pd = to_dev(u), to_dev(p)
+    lat.md_trajectory(ud, pd, None, 1.0, 1, beta=0.0, n_f=0.0)
+    ref = O.expi_su3(p, 1.0) @ u
+    # two moves, each a few ten roundings of unit-size entries
+    assert float((ud.cpu() - ref).abs().max()) < 2e-14
+    assert torch.equal(pd.cpu(), p)
+    lat.close()
+
+
+def test_long_trajectory_equals_its_parts():
+    """70 pure-gauge steps (more than the actions held at a time) against ten at a time."""
+    dims, n = (2, 6, 4, 2), 70
+    lat = Lattice(dims, KAPPA, CSW)
+    ends = []
+    for part in (n, 10):
+        u, p, acts = to_dev(synth.random_su3_field(dims, 0.3, 6)), to_dev(synth.momenta(dims, 6)), []
+        for _ in range(n // part):
+            acts += lat.md_trajectory(u, p, None, 0.02, part, beta=BETA, n_f=0.0, reunitarize=True)[0]
+        ends.append((u, p, torch.tensor(acts, dtype=torch.float64)))
+    for a, b in zip(*ends):
+        assert float((a.cpu() - b.cpu()).abs().max() / b.abs().max()) < 1e-13
+    lat.close()
+
+
+def test_copies_after_a_failed_trajectory():
+    """A trajectory that stops with QCD_ECLOVER leaves links whose every copy agrees."""
+    from paper_0910_0262_amd import QCDError
+
+    dims = (4, 4, 4, 4)
+    u, p = to_dev(synth.random_su3_field(dims, 1.0, 1)), to_dev(synth.momenta(dims, 1))
+    xi = to_dev(synth.heatbath_xi(dims, 1))[None]
+    lat = Lattice(dims, 0.2, 5.0)
+    with pytest.raises(QCDError) as err:
+        lat.md_trajectory(u, p, xi, 0.1, 1, beta=BETA, n_f=1.0, prec="mixed")
+    assert err.value.status == "QCD_ECLOVER"
+    moved = lat.store_gauge()
+    assert float((moved - u).abs().max()) > 1e-3
+    lat.set_params(0.1, 0.5)
+    lat.build_clover()
+    fresh = Lattice(dims, 0.1, 0.5)
+    fresh.load_gauge(moved)
+    b = to_dev(synth.gaussian_source(dims, 1, 0))
+    bs = torch.stack([b, 2.0 * b, -b])
+    for prec in ("fp64", "mixed"):
+        assert torch.equal(lat.solve(b, prec=prec)[0], fresh.solve(b, prec=prec)[0])
+        assert torch.equal(lat.solve_multi(bs, prec=prec)[0], fresh.solve_multi(bs, prec=prec)[0])
+    lat.close()
+    fresh.close()
