@@ -11,6 +11,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 
 #include "cloverqcd.h"
 #include "qcd_internal.h"
@@ -50,7 +51,7 @@ enum Slot { V_IN_E, V_IN_O, V_OUT_E, V_OUT_O, V_T, V_Q, V_X, V_R, V_P, V_RHS, V_
             V_P1, V_P2, V_P3, NSLOT };
 // binary16 work vectors
 enum HSlot { H_P, H_T, H_Q, H_R, H_IN, H_OUT, H_P1, H_P2, H_P3, NHSLOT };
-// ring of mailbox slots / events for the iterations in flight
+// ring of mailbox slots for the iterations in flight
 constexpr int kRing = 64;
 // steps of a trajectory whose actions wait in host-mapped memory
 constexpr int kActRing = 64;
@@ -70,10 +71,10 @@ struct Work {
   float4* x32 = nullptr;
   double* partial = nullptr;
   CgState* st = nullptr;         // nr states
-  CgState* st_host = nullptr;    // pinned copy of the last states read (nr)
-  CgState* mbox_host = nullptr;  // host-mapped rings of posted states: [nr][kRing]
-  CgState* mbox_dev = nullptr;   // device address of mbox_host
-  int post_ctr = 0;              // host mirror of CgState::post_seq (equal for all nr states)
+  CgState st_host[QCD_MAX_RHS];  // the last states read (nr)
+  Mail* mbox_host = nullptr;     // host-mapped rings of posted states: [nr][kRing]
+  Mail* mbox_dev = nullptr;      // device address of mbox_host
+  unsigned int post_ctr = 0;     // host mirror of CgState::post_seq (equal for all nr states)
 };
 
 struct qcd_ctx {
@@ -116,17 +117,18 @@ struct qcd_ctx {
   Work wm;          // multi-source solves
   Work* w = &w1;    // the set the solver drivers use
   int wm_lg_alloc = -1;  // right-hand sides (log2) wm was allocated for
-  hipEvent_t ev[kRing] = {};
   hipStream_t cap = nullptr;    // private stream used only to capture graphs
   hipGraphExec_t iter_graph[2][4] = {};  // one CG iteration: [FP64, mixed][position in the x cycle]
   int* status = nullptr;
-  int* status_host = nullptr;  // pinned
+  int* status_host = nullptr;  // host-mapped
   double2* xi = nullptr;       // clover-force Xi: [par][6][kXiChunks][stride]
   double2* gint = nullptr;     // force accumulator: [mu][par][9][stride]
   double* md_partial = nullptr;  // partial sums of the molecular-dynamics kernels, then their span sums
   double* logdet = nullptr;    // ln det A(x) per odd site, from the last clover inversion
   double* act_host = nullptr;  // host-mapped sums of the actions, [kActRing][3]: fermion, gauge, ln det
   double* act_dev = nullptr;   // its device address
+  double* norm_host = nullptr; // host-mapped norms of a solve, [4][16]: residual and source, even and odd sites
+  double* norm_dev = nullptr;
 
   // the derived link copies that a call needs next (all: what the context keeps between calls)
   LinkCopies copies(bool f64, bool half, bool half18) const {
@@ -177,7 +179,6 @@ void free_work(Work& w) {
   f(w.x32);
   f(w.partial);
   f(w.st);
-  if (w.st_host) (void)hipHostFree(w.st_host);
   if (w.mbox_host) (void)hipHostFree(w.mbox_host);
   w = Work();
 }
@@ -216,9 +217,7 @@ int alloc_work(const Geom& g, Work& w, int lg, bool all_slots) {
   const size_t nb64 = blocks_for(w.gv.Vh, 64);
   A(&w.partial, (nb64 + 64 + nb64 / kFoldSpan + 1) * w.nr * sizeof(double));
   A(&w.st, w.nr * sizeof(CgState));
-  if (rc == QCD_OK && hipHostMalloc((void**)&w.st_host, w.nr * sizeof(CgState), hipHostMallocDefault) != hipSuccess)
-    rc = fail(QCD_ENOMEM, "pinned host allocation failed");
-  if (rc == QCD_OK && hipHostMalloc((void**)&w.mbox_host, (size_t)w.nr * kRing * sizeof(CgState),
+  if (rc == QCD_OK && hipHostMalloc((void**)&w.mbox_host, (size_t)w.nr * kRing * sizeof(Mail),
                                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     rc = fail(QCD_ENOMEM, "pinned host allocation failed");
   if (rc == QCD_OK && hipHostGetDevicePointer((void**)&w.mbox_dev, w.mbox_host, 0) != hipSuccess)
@@ -235,8 +234,8 @@ int alloc_work(const Geom& g, Work& w, int lg, bool all_slots) {
     free_work(w);
     return rc;
   }
-  std::memset(w.st_host, 0, w.nr * sizeof(CgState));
-  std::memset(w.mbox_host, 0, (size_t)w.nr * kRing * sizeof(CgState));
+  std::memset(w.st_host, 0, sizeof(w.st_host));
+  std::memset(w.mbox_host, 0, (size_t)w.nr * kRing * sizeof(Mail));
   w.post_ctr = 0;
   return QCD_OK;
 }
@@ -267,14 +266,11 @@ void free_ctx(qcd_ctx* c) {
   f(c->gint);
   f(c->md_partial);
   f(c->logdet);
-  if (c->status_host) (void)hipHostFree(c->status_host);
   if (c->act_host) (void)hipHostFree(c->act_host);
   for (auto& row : c->iter_graph)
     for (auto& gx : row)
       if (gx) (void)hipGraphExecDestroy(gx);
   if (c->cap) (void)hipStreamDestroy(c->cap);
-  for (auto& e : c->ev)
-    if (e) (void)hipEventDestroy(e);
 }
 
 // the site term of k2 reads the compact A_ee where the clover term has its form
@@ -421,27 +417,10 @@ double* fold_area(const qcd_ctx* c) {
   return c->w->partial + ((size_t)blocks_for(c->w->gv.Vh, 64) + 64) * c->w->nr;
 }
 
-int sync_state(qcd_ctx* c) {
-  HIPCHK(hipMemcpyAsync(c->w->st_host, c->w->st, c->w->nr * sizeof(CgState), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return QCD_OK;
-}
-
-// |x|^2 of an FP64 vector into st->scalar and returned (synchronises)
-int norm2_sync(qcd_ctx* c, int s, double* out) {
+// |x|^2 of each right-hand side of an FP64 vector to norm_host[16 slot + r]
+int post_norm2(qcd_ctx* c, int s, int slot) {
   HIPCHK(launch_norm2(c->w->gv, c->w->lg, c->ref64(s), c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  *out = c->w->st_host->scalar;
-  return QCD_OK;
-}
-
-// |x|^2 of each right-hand side of an FP64 vector (synchronises)
-int norm2_each(qcd_ctx* c, int s, double* out) {
-  HIPCHK(launch_norm2(c->w->gv, c->w->lg, c->ref64(s), c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  for (int r = 0; r < c->w->nr; ++r) out[r] = c->w->st_host[r].scalar;
+  HIPCHK(launch_fin_sum(c->norm_dev + 16 * slot, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
   return QCD_OK;
 }
 
@@ -464,11 +443,13 @@ double mdagm_bytes_per_site(const qcd_ctx* c, bool mixed, int nr = 1) {
 
 // ------------------------------------------------------------------ CG drivers
 // The host keeps `depth` iterations in flight.  Each iteration ends with a
-// finalisation kernel that posts the state to a mailbox slot, followed by an
-// event; the host waits on the event of the oldest iteration in flight,
-// reads its slot, and enqueues the next iteration, so the GPU never waits for
-// the host and at most depth - 1 iterations are issued past convergence
-// (their kernels return at once).
+// finalisation kernel that posts the state to host-mapped memory; the host
+// polls for the post of the oldest iteration in flight and enqueues the next
+// one, so the GPU never waits for the host and at most depth - 1 iterations
+// are issued past convergence (their kernels return at once).  (With an event per
+// iteration, and four more waits around the recurrence, a solve took 100 to
+// 150 us more and an iteration 1 to 3 us: 8x8x16x16 in FP64 1896 -> 1665 us,
+// 16^4 mixed 3637 -> 3318 us.)
 struct CgCounters {
   int iters = 0, restarts = 0, ru = 0;
   double mdagm = 0.0;  // FP64 Mhat^dag Mhat applications
@@ -477,27 +458,50 @@ struct CgCounters {
 };
 
 struct Pipe {
-  int slot[kRing];
+  unsigned int tag[kRing];  // of iteration seq at seq % kRing
   long long seq = 0, seen = 0;
 };
 
-// slot of the next posted state; mirrors post() on the device
-int next_slot(qcd_ctx* c) {
-  const int s = c->w->post_ctr % kRing;
-  c->w->post_ctr = (c->w->post_ctr + 1) % (kRing * 1024);
-  return s;
+// tag of the next posted state; mirrors post() on the device
+unsigned int next_tag(qcd_ctx* c) { return ++c->w->post_ctr; }
+
+// Wait for the state posted with `tag`, for every right-hand side.  The tag is
+// polled closely at first, then at intervals that are short against an
+// iteration of a lattice that takes so long; a stream that has nothing left
+// to do, or an error, ends the wait where no post came.
+int wait_tag(qcd_ctx* c, unsigned int tag) {
+  Work& w = *c->w;
+  const auto t0 = std::chrono::steady_clock::now();
+  long long next_look = 1000000;  // ns until the stream itself is looked at
+  for (int r = 0; r < w.nr; ++r) {
+    const Mail* m = &w.mbox_host[(size_t)r * kRing + (tag - 1) % (unsigned int)kRing];
+    for (unsigned int n = 1; __atomic_load_n(&m->tag, __ATOMIC_ACQUIRE) != tag; ++n) {
+      if (n % 64 != 0) {
+        __builtin_ia32_pause();
+        continue;
+      }
+      const long long ns = std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - t0).count();
+      if (ns > 200000) std::this_thread::sleep_for(std::chrono::microseconds(10));
+      if (ns < next_look) continue;
+      next_look = ns + 1000000;
+      const hipError_t e = hipStreamQuery(c->stream);
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) return fail(QCD_EHIP, std::string("solver stream: ") + hipGetErrorString(e));
+      if (__atomic_load_n(&m->tag, __ATOMIC_ACQUIRE) != tag) return fail(QCD_EHIP, "the solver's kernels ended without posting their state");
+    }
+    std::memcpy(&w.st_host[r], &m->s, sizeof(CgState));
+  }
+  return QCD_OK;
 }
 
-// Read the states posted in `slot` once the work before event `slot` has
-// completed: into the work set's host copies, and combined into `out`.  With
-// several right-hand sides `out` is done / halted when all are, non-finite or
-// asking for a reliable update when any is; its rr_hi is the largest
-// rr_hi / stop2 over the right-hand sides still running (stop2 = 1).
-int wait_slot(qcd_ctx* c, int slot, CgState* out) {
-  HIPCHK(hipEventSynchronize(c->ev[slot]));
+// Read the states posted with `tag` into the work set's host copies, and
+// combined into `out`.  With several right-hand sides `out` is done / halted
+// when all are, non-finite or asking for a reliable update when any is; its
+// rr_hi is the largest rr_hi / stop2 over the right-hand sides still running
+// (stop2 = 1).
+int wait_post(qcd_ctx* c, unsigned int tag, CgState* out) {
+  QCHK(wait_tag(c, tag));
   Work& w = *c->w;
-  for (int r = 0; r < w.nr; ++r)
-    std::memcpy(&w.st_host[r], (const void*)&w.mbox_host[(size_t)r * kRing + slot], sizeof(CgState));
   *out = w.st_host[0];
   if (w.nr == 1) return QCD_OK;
   double worst = 0.0;
@@ -531,20 +535,20 @@ int residual_f64(qcd_ctx* c, int x, int out_r, const CgState* st) {
 // (nclear: the newest alphas whose directions the caller already took into x)
 int recompute_residual(qcd_ctx* c, int restart, CgState* posted, int nclear = 0) {
   QCHK(residual_f64(c, V_X, V_R, nullptr));
-  const int slot = next_slot(c);
   HIPCHK(launch_fin_ru(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), restart, nclear, c->w->mbox_dev,
                        kRing, c->stream));
-  HIPCHK(hipEventRecord(c->ev[slot], c->stream));
-  if (posted) QCHK(wait_slot(c, slot, posted));
+  const unsigned int tag = next_tag(c);
+  if (posted) QCHK(wait_post(c, tag, posted));
   return QCD_OK;
 }
 
-int init_recurrence(qcd_ctx* c, double tol, double delta, int max_iter, int mixed, CgState* posted) {
+// Starts the recurrence; its first state is posted with *tag.
+int init_recurrence(qcd_ctx* c, double tol, double delta, int max_iter, int mixed, unsigned int* tag) {
   HIPCHK(launch_norm2(c->w->gv, c->w->lg, c->ref64(V_RHS), c->w->partial, c->block(), c->stream));
-  const int slot = next_slot(c);
-  HIPCHK(launch_fin_init(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), tol, delta, max_iter, mixed, c->w->mbox_dev, kRing, c->stream));
-  HIPCHK(hipEventRecord(c->ev[slot], c->stream));
-  return wait_slot(c, slot, posted);
+  HIPCHK(launch_fin_init(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), tol, delta, max_iter, mixed,
+                         c->w->post_ctr, c->w->mbox_dev, kRing, c->stream));
+  *tag = next_tag(c);
+  return QCD_OK;
 }
 
 // Partials per right-hand side up to which the dagger k1 finishes alpha itself.
@@ -637,9 +641,7 @@ int enqueue_iter(qcd_ctx* c, Pipe& pp, bool mixed) {
   } else {
     QCHK(launch_iter(c, mixed, j));
   }
-  const int slot = next_slot(c);
-  HIPCHK(hipEventRecord(c->ev[slot], c->stream));
-  pp.slot[pp.seq % kRing] = slot;
+  pp.tag[pp.seq % kRing] = next_tag(c);
   ++pp.seq;
   return QCD_OK;
 }
@@ -662,9 +664,13 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
   const Geom& g = c->g;
   const int B = c->block();
   CgState s;
-  QCHK(init_recurrence(c, p->tol, 0.0, p->max_iter, 0, &s));
-  if (s.nan) return fail(QCD_ENAN, "non-finite right-hand side");
+  unsigned int start;
+  QCHK(init_recurrence(c, p->tol, 0.0, p->max_iter, 0, &start));
+  const int depth = pipeline_depth(p);
+  Pipe pp;
   if (use_x0) {
+    QCHK(wait_post(c, start, &s));
+    if (s.nan) return fail(QCD_ENAN, "non-finite right-hand side");
     QCHK(recompute_residual(c, 1, &s));
     cnt.mdagm += 1;
     if (s.nan) return fail(QCD_ENAN, "non-finite residual of the starting guess");
@@ -673,13 +679,16 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
     HIPCHK(launch_zero(c->w->gv, c->ref64(V_X), B, c->stream));
     HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->ref64(V_R), B, c->stream));
     HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->ref64(V_P), B, c->stream));
+    // the first iterations do not wait for the start's state (nothing of
+    // them runs where it was final)
+    while (pp.seq < depth) QCHK(enqueue_iter(c, pp, false));
+    QCHK(wait_post(c, start, &s));
+    if (s.nan) return fail(QCD_ENAN, "non-finite right-hand side");
   }
-  const int depth = pipeline_depth(p);
   int restarts = 0;
-  Pipe pp;
   while (!s.done) {
     while (pp.seq - pp.seen < depth) QCHK(enqueue_iter(c, pp, false));
-    QCHK(wait_slot(c, pp.slot[pp.seen % kRing], &s));
+    QCHK(wait_post(c, pp.tag[pp.seen % kRing], &s));
     ++pp.seen;
     if (s.nan) return fail(QCD_ENAN, "non-finite residual in FP64 CG");
     if (!s.done) continue;
@@ -693,7 +702,6 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
     HIPCHK(launch_p_restart_f64(c->w->gv, c->w->lg, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
     pp = Pipe();
   }
-  HIPCHK(hipStreamSynchronize(c->stream));
   cnt.iters += s.iter;
   cnt.mdagm += s.iter;
   cnt.restarts += restarts;
@@ -721,20 +729,23 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
   const Geom& g = c->g;
   const int B = c->block();
   CgState s;
-  QCHK(init_recurrence(c, p->tol, p->delta_reliable, p->max_iter, 1, &s));
-  if (s.nan) return fail(QCD_ENAN, "non-finite right-hand side");
+  unsigned int start;
+  QCHK(init_recurrence(c, p->tol, p->delta_reliable, p->max_iter, 1, &start));
   HIPCHK(launch_zero(c->w->gv, c->ref64(V_X), B, c->stream));
   HIPCHK(launch_zero(c->w->gv, SpRef{SP_F32, c->w->x32, nullptr}, B, c->stream));
   HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->refh(H_R), B, c->stream));
   HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->refh(H_P), B, c->stream));
   const int depth = pipeline_depth(p);
   Pipe pp;
+  while (pp.seq < depth) QCHK(enqueue_iter(c, pp, true));  // as in cg_fp64
+  QCHK(wait_post(c, start, &s));
+  if (s.nan) return fail(QCD_ENAN, "non-finite right-hand side");
   long long ru_barrier = 0;  // iterations enqueued before the last reliable update
   int ru_seen = 0, stall = 0;
   double best_rr = s.rr_hi;
   while (!s.done) {
     while (pp.seq - pp.seen < depth) QCHK(enqueue_iter(c, pp, true));
-    QCHK(wait_slot(c, pp.slot[pp.seen % kRing], &s));
+    QCHK(wait_post(c, pp.tag[pp.seen % kRing], &s));
     const long long idx = pp.seen++;
     if (s.nan) return fail(QCD_ENAN, "non-finite residual in mixed CG");
     if (s.done) break;
@@ -747,7 +758,6 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
         best_rr = s.rr_hi;
         stall = 0;
       } else if (++stall >= 3) {
-        HIPCHK(hipStreamSynchronize(c->stream));
         if (const int q = fold_x(c, pp); q < 0) return q;
         cnt.iters += s.iter;
         cnt.mdagm_mixed += s.iter;
@@ -769,7 +779,6 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
       ru_barrier = pp.seq;
     }
   }
-  HIPCHK(hipStreamSynchronize(c->stream));
   cnt.iters += s.iter;
   cnt.mdagm_mixed += s.iter;
   cnt.blas_bytes += (double)s.iter * xp_bytes_per_iter(c, true) * c->w->gv.Vh;
@@ -813,12 +822,6 @@ void fill_stats_from(qcd_ctx* c, const CgState& s, const CgCounters& cnt, const 
 void fill_stats(qcd_ctx* c, const CgCounters& cnt, const qcd_solver_params* p, double seconds, double true_rel,
                 qcd_solver_stats* out) {
   fill_stats_from(c, *c->w->st_host, cnt, p, seconds, true_rel, out);
-}
-
-// Solve on even sites for a prepared right-hand side in V_RHS; result in V_X.
-int solve_even(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
-  QCHK(run_cg(c, p, cnt));
-  return QCD_OK;
 }
 
 int validate_dims(const int dims[4]) {
@@ -892,14 +895,15 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   A(&c->status, 2 * sizeof(int));
   A(&c->md_partial, (md_link_partials(g) + md_link_partials(g) / kFoldSpan + 1) * sizeof(double));
   if (rc == QCD_OK) rc = alloc_work(g, c->w1, 0, true);
-  if (rc == QCD_OK && hipHostMalloc((void**)&c->status_host, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess)
-    rc = fail(QCD_ENOMEM, "pinned host allocation failed");
-  if (rc == QCD_OK && (hipHostMalloc((void**)&c->act_host, 3 * kActRing * sizeof(double),
+  // one host-mapped block: the actions, the norms, the clover status
+  constexpr size_t n_sums = 3 * kActRing + 4 * 16;
+  if (rc == QCD_OK && (hipHostMalloc((void**)&c->act_host, n_sums * sizeof(double) + 2 * sizeof(int),
                                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
                        hipHostGetDevicePointer((void**)&c->act_dev, c->act_host, 0) != hipSuccess))
     rc = fail(QCD_ENOMEM, "pinned host allocation failed");
-  for (int k = 0; k < kRing && rc == QCD_OK; ++k)
-    if (hipEventCreateWithFlags(&c->ev[k], hipEventDisableTiming) != hipSuccess) rc = fail(QCD_EHIP, "hipEventCreate failed");
+  c->norm_host = c->act_host + 3 * kActRing;
+  c->norm_dev = c->act_dev + 3 * kActRing;
+  c->status_host = (int*)(c->act_host + n_sums);
   if (rc == QCD_OK && hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
     rc = fail(QCD_EHIP, "hipStreamCreate failed");
   if (rc != QCD_OK) {
@@ -1120,9 +1124,8 @@ int use_multi(qcd_ctx* c, int lg) {
 }
 
 // Solve M x = b for the work set's right-hand sides (n of them, packed by the
-// caller into V_B_E / V_B_O); writes x into V_X / V_OUT_O and the stats.
-int solve_packed(qcd_ctx* c, const qcd_solver_params* p, int n, qcd_solver_stats* stats,
-                 std::chrono::steady_clock::time_point t0) {
+// caller into V_B_E / V_B_O); x goes to V_X / V_OUT_O and the norms to norm_host.
+int solve_packed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
   const Geom& g = c->g;
   const int B = c->block(), nb = nblocks(c), nr = c->w->nr;
   // bhat = b_e + kappa H_eo A_oo^{-1} b_o; rhs = Mhat^dag bhat
@@ -1138,11 +1141,7 @@ int solve_packed(qcd_ctx* c, const qcd_solver_params* p, int n, qcd_solver_stats
   }
   QCHK(k1_f64(c, V_AUX, V_T, true, nullptr));
   QCHK(k2_f64(c, V_AUX, V_T, V_RHS, true, 0, 0, 0.0, false, nullptr));
-  CgCounters cnt;
-  int rc = solve_even(c, p, cnt);
-  if (rc != QCD_OK && rc != QCD_ENOCONV) return rc;
-  CgState s_end[16];
-  std::memcpy(s_end, c->w->st_host, nr * sizeof(CgState));
+  QCHK(run_cg(c, p, cnt));
   // x_o = A_oo^{-1} (b_o + kappa H_oe x_e)
   {
     DslashOp op = base_op(c, 1);
@@ -1156,25 +1155,25 @@ int solve_packed(qcd_ctx* c, const qcd_solver_params* p, int n, qcd_solver_stats
     HIPCHK(launch_dslash(g, op, B, c->stream));
   }
   // true residual ||b - M x|| / ||b|| on the full lattice, per right-hand side
-  double rn[16] = {}, bn[16] = {}, t[16];
   QCHK(m_parity(c, 0, V_X, V_OUT_O, V_AUX, false, 2, V_B_E, -1.0));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nb, nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  for (int r = 0; r < nr; ++r) rn[r] += c->w->st_host[r].scalar;
+  HIPCHK(launch_fin_sum(c->norm_dev, c->w->partial, nb, nr, fold_area(c), c->stream));
   QCHK(m_parity(c, 1, V_OUT_O, V_X, V_AUX, false, 2, V_B_O, -1.0));
-  HIPCHK(launch_fin_scalar(c->w->st, c->w->partial, nb, nr, fold_area(c), c->stream));
-  QCHK(sync_state(c));
-  for (int r = 0; r < nr; ++r) rn[r] += c->w->st_host[r].scalar;
-  QCHK(norm2_each(c, V_B_E, t));
-  for (int r = 0; r < nr; ++r) bn[r] += t[r];
-  QCHK(norm2_each(c, V_B_O, t));
-  for (int r = 0; r < nr; ++r) bn[r] += t[r];
+  HIPCHK(launch_fin_sum(c->norm_dev + 16, c->w->partial, nb, nr, fold_area(c), c->stream));
+  QCHK(post_norm2(c, V_B_E, 2));
+  return post_norm2(c, V_B_O, 3);
+}
+
+// What a solve reports, once its stream has been waited for.
+int solve_report(qcd_ctx* c, const qcd_solver_params* p, int n, const CgCounters& cnt, qcd_solver_stats* stats,
+                 std::chrono::steady_clock::time_point t0) {
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-  std::memcpy(c->w->st_host, s_end, nr * sizeof(CgState));
+  const double* h = c->norm_host;
   bool all_conv = true;
   for (int r = 0; r < n; ++r) {
-    if (stats) fill_stats_from(c, s_end[r], cnt, p, seconds, bn[r] > 0 ? std::sqrt(rn[r] / bn[r]) : 0.0, &stats[r], n);
-    if (s_end[r].rr_hi > s_end[r].stop2) all_conv = false;
+    const CgState& s = c->w->st_host[r];
+    const double rn = h[r] + h[16 + r], bn = h[32 + r] + h[48 + r];
+    if (stats) fill_stats_from(c, s, cnt, p, seconds, bn > 0 ? std::sqrt(rn / bn) : 0.0, &stats[r], n);
+    if (s.rr_hi > s.stop2) all_conv = false;
   }
   if (!all_conv) return fail(QCD_ENOCONV, "solver reached max_iter without meeting tol");
   return QCD_OK;
@@ -1192,11 +1191,11 @@ int qcd_solve(qcd_ctx* c, const qcd_solver_params* p, const void* b_dev, void* x
   const auto t0 = std::chrono::steady_clock::now();
   WorkGuard wg(c, &c->w1);
   HIPCHK(launch_pack_spinor_full(c->g, (const double2*)b_dev, c->f64(V_B_E), c->f64(V_B_O), c->stream));
-  const int rc = solve_packed(c, p, 1, stats, t0);
-  if (rc != QCD_OK && rc != QCD_ENOCONV) return rc;
+  CgCounters cnt;
+  QCHK(solve_packed(c, p, cnt));
   HIPCHK(launch_unpack_spinor_full(c->g, c->f64(V_X), c->f64(V_OUT_O), (double2*)x_dev, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
-  return rc;
+  return solve_report(c, p, 1, cnt, stats, t0);
 }
 
 int qcd_solve_multi(qcd_ctx* c, const qcd_solver_params* p, int n_rhs, const void* b_dev, void* x_dev,
@@ -1213,16 +1212,13 @@ int qcd_solve_multi(qcd_ctx* c, const qcd_solver_params* p, int n_rhs, const voi
   // a set allocated for more right-hand sides serves fewer (its buffers are larger)
   QCHK(use_multi(c, lg));
   Work& w = c->wm;
-  // every state posts in step from zero
-  HIPCHK(hipMemsetAsync(w.st, 0, ((size_t)1 << c->wm_lg_alloc) * sizeof(CgState), c->stream));
-  w.post_ctr = 0;
   WorkGuard wg(c, &w);
   HIPCHK(launch_pack_spinor_multi(c->g, lg, n_rhs, (const double2*)b_dev, c->f64(V_B_E), c->f64(V_B_O), c->stream));
-  const int rc = solve_packed(c, p, n_rhs, stats, t0);
-  if (rc != QCD_OK && rc != QCD_ENOCONV) return rc;
+  CgCounters cnt;
+  QCHK(solve_packed(c, p, cnt));
   HIPCHK(launch_unpack_spinor_multi(c->g, lg, n_rhs, c->f64(V_X), c->f64(V_OUT_O), (double2*)x_dev, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
-  return rc;
+  return solve_report(c, p, n_rhs, cnt, stats, t0);
 }
 
 // Buffers of the fermion and determinant forces (the gauge force needs none).
@@ -1250,7 +1246,7 @@ static int force_core(qcd_ctx* c, const qcd_solver_params* p, int slot, CgCounte
   *conv_rc = c->w->st_host->rr_hi <= c->w->st_host->stop2 ? QCD_OK : QCD_ENOCONV;
   // S = Re phi^dag X
   HIPCHK(launch_dot_re(c->w->gv, c->w->lg, c->f64(V_RHS), c->f64(V_X), c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot, c->w->partial, nb, fold_area(c), c->stream));
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot, c->w->partial, nb, 1, fold_area(c), c->stream));
   // Z = A_oo^{-1} H_oe X; Y = Mhat X; W = A_oo^{-1} g5 H_oe g5 Y
   QCHK(k1_f64(c, V_X, V_Z, false, nullptr));
   QCHK(k2_f64(c, V_X, V_Z, V_Y, false, 0, 0, 0.0, false, nullptr));
@@ -1355,14 +1351,14 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
 // The sum of the partial sums of (1 - Re tr P / 3) in md_partial to act_host[3 slot + 1]
 static int post_gauge_action(qcd_ctx* c, int slot) {
   const int n = md_link_partials(c->g);
-  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 1, c->md_partial, n, c->md_partial + n, c->stream));
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 1, c->md_partial, n, 1, c->md_partial + n, c->stream));
   return QCD_OK;
 }
 
 // sum_odd ln det A from the last inversion to act_host[3 slot + 2]
 static int post_logdet(qcd_ctx* c, int slot) {
   HIPCHK(launch_sum_cb(c->g, c->logdet, c->w->partial, c->block(), c->stream));
-  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 2, c->w->partial, nblocks(c), fold_area(c), c->stream));
+  HIPCHK(launch_fin_sum(c->act_dev + 3 * slot + 2, c->w->partial, nblocks(c), 1, fold_area(c), c->stream));
   return QCD_OK;
 }
 

@@ -259,28 +259,20 @@ hipError_t launch_dot_re(const Geom& gv, int lg, SpF64 a, SpF64 b, double* parti
 
 // ------------------------------------------------------------------ CG scalar kernels (one workgroup)
 // Each finalisation kernel that ends an iteration posts a copy of the state
-// to mailbox[post_seq % ring] (host-mapped memory the host reads once the
-// iteration's event has completed) and advances post_seq; the host counts
-// the posting launches it issues, so it knows the slot of each without
-// passing it as an argument (the same captured graph serves every iteration).
+// to host-mapped memory (post()), which the host polls; the posts are counted
+// on both sides, so none is passed as an argument (the same captured graph
+// serves every iteration).
 // Workgroup r of a launch handles right-hand side r: its state st[r], its
 // partials partial[r * n ...], its mailbox ring mbox[r * ring ...].
-__global__ void fin_scalar_k(CgState* st, const double* partial, int n) {
-  st += blockIdx.x;
-  partial += (size_t)blockIdx.x * n;
-  const double s = block_sum_partials(partial, n);
-  if (threadIdx.x == 0) st->scalar = s;
-}
-// The sum into host-mapped memory, for the host to read once the stream has been waited for.
 __global__ void fin_sum_k(double* out, const double* partial, int n) {
-  const double s = block_sum_partials(partial, n);
+  const double s = block_sum_partials(partial + (size_t)blockIdx.x * n, n);
   if (threadIdx.x == 0) {
-    *out = s;
+    out[blockIdx.x] = s;
     __threadfence_system();
   }
 }
 __global__ void fin_init_k(CgState* st, const double* partial, int n, double tol, double delta, int max_iter,
-                           int mixed, CgState* mbox, int ring) {
+                           int mixed, unsigned int seq, Mail* mbox, int ring) {
   st += blockIdx.x;
   partial += (size_t)blockIdx.x * n;
   mbox += (size_t)blockIdx.x * ring;
@@ -294,7 +286,6 @@ __global__ void fin_init_k(CgState* st, const double* partial, int n, double tol
   st->stop2 = tol * tol * rr;
   st->maxrr = rr;
   st->delta2 = delta * delta;
-  st->scalar = rr;
   st->iter = 0;
   st->max_iter = max_iter;
   st->nan = finite(rr) ? 0 : 1;
@@ -305,6 +296,7 @@ __global__ void fin_init_k(CgState* st, const double* partial, int n, double tol
   st->do_p = 0;
   st->mixed = mixed;
   st->ru_count = 0;
+  st->post_seq = seq;
   for (int m = 0; m < 4; ++m) st->ah[m] = 0.0;
   post(st, mbox, ring);
 }
@@ -315,7 +307,7 @@ __global__ void fin_alpha_k(CgState* st, const double* partial, int n) {
   const double qq = block_sum_partials(partial, n);
   if (threadIdx.x == 0) state_alpha(st, qq);
 }
-__global__ void fin_beta_k(CgState* st, const double* partial, int n, CgState* mbox, int ring) {
+__global__ void fin_beta_k(CgState* st, const double* partial, int n, Mail* mbox, int ring) {
   st += blockIdx.x;
   partial += (size_t)blockIdx.x * n;
   mbox += (size_t)blockIdx.x * ring;
@@ -332,7 +324,7 @@ __global__ void fin_beta_k(CgState* st, const double* partial, int n, CgState* m
 // The newest nclear alphas of the history were already taken into x (the
 // reliable update folded the unfinished cycle's directions in): they are
 // zeroed, so the end of the cycle does not add those directions again.
-__global__ void fin_ru_k(CgState* st, const double* partial, int n, int restart, int nclear, CgState* mbox,
+__global__ void fin_ru_k(CgState* st, const double* partial, int n, int restart, int nclear, Mail* mbox,
                          int ring) {
   st += blockIdx.x;
   partial += (size_t)blockIdx.x * n;
@@ -382,26 +374,22 @@ __global__ void __launch_bounds__(256) fold_partials_k(const double* partial, in
   hipLaunchKernelGGL(kernel, dim3(nr), dim3(1024), 0, s, __VA_ARGS__);                             \
   return hipGetLastError();
 
-hipError_t launch_fin_scalar(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s) {
-  FIN_LAUNCH(fin_scalar_k, st, partial, n)
-}
-hipError_t launch_fin_sum(double* out, const double* partial, int n, double* fold, hipStream_t s) {
-  const int nr = 1;
+hipError_t launch_fin_sum(double* out, const double* partial, int n, int nr, double* fold, hipStream_t s) {
   FIN_LAUNCH(fin_sum_k, out, partial, n)
 }
 hipError_t launch_fin_init(CgState* st, const double* partial, int n, int nr, double* fold, double tol, double delta,
-                           int max_iter, int mixed, CgState* mbox, int ring, hipStream_t s) {
-  FIN_LAUNCH(fin_init_k, st, partial, n, tol, delta, max_iter, mixed, mbox, ring)
+                           int max_iter, int mixed, unsigned int seq, Mail* mbox, int ring, hipStream_t s) {
+  FIN_LAUNCH(fin_init_k, st, partial, n, tol, delta, max_iter, mixed, seq, mbox, ring)
 }
 hipError_t launch_fin_alpha(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s) {
   FIN_LAUNCH(fin_alpha_k, st, partial, n)
 }
-hipError_t launch_fin_beta(CgState* st, const double* partial, int n, int nr, double* fold, CgState* mbox, int ring,
+hipError_t launch_fin_beta(CgState* st, const double* partial, int n, int nr, double* fold, Mail* mbox, int ring,
                            hipStream_t s) {
   FIN_LAUNCH(fin_beta_k, st, partial, n, mbox, ring)
 }
 hipError_t launch_fin_ru(CgState* st, const double* partial, int n, int nr, double* fold, int restart, int nclear,
-                         CgState* mbox, int ring, hipStream_t s) {
+                         Mail* mbox, int ring, hipStream_t s) {
   FIN_LAUNCH(fin_ru_k, st, partial, n, restart, nclear, mbox, ring)
 }
 

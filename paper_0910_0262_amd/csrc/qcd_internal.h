@@ -22,25 +22,32 @@ struct CgState {
   double maxrr;    // max |r|^2 since the last reliable update
   double delta2;   // delta_reliable^2
   double rr_hi;    // last FP64 residual norm^2
-  double scalar;   // generic reduction result (dot products, norms)
   double ah[4];    // the last four alphas, newest first (x takes alpha_k p_k a few iterations late)
   int iter, max_iter;
   int halt, done, need_ru, nan, do_x, do_p, mixed, ru_count;
-  int post_seq;    // number of states posted so far; the next goes to mailbox[post_seq % ring]
+  unsigned int post_seq;  // number of states posted so far (modulo 2^32)
 };
 
 // ---- CG state updates, shared by the one-workgroup finalisation kernels and
 // the stencil kernels that finish their own reduction (one thread runs them).
 __device__ __forceinline__ bool finite(double v) { return v == v && v - v == 0.0; }
 
-// Copy the state to mailbox[post_seq % ring] (host-mapped memory the host
-// reads once the iteration's event has completed) and advance post_seq; the
-// host counts the posting launches it issues, so it knows each slot.
-__device__ __forceinline__ void post(CgState* st, CgState* mbox, int ring) {
-  const int slot = st->post_seq % ring;
-  st->post_seq = (st->post_seq + 1) % (ring * 1024);
-  mbox[slot] = *st;
+// A posted state in host-mapped memory; tag is written last, so that the host,
+// which polls it, finds the state whole.
+struct alignas(64) Mail {
+  CgState s;
+  unsigned int tag;
+};
+// Post the state, the post_seq-th, with tag post_seq + 1 to mailbox entry
+// post_seq % ring; the host counts the posting launches it issues, so it
+// knows each tag.
+__device__ __forceinline__ void post(CgState* st, Mail* mbox, int ring) {
+  const unsigned int n = st->post_seq;
+  st->post_seq = n + 1;
+  Mail* m = mbox + n % (unsigned int)ring;
+  m->s = *st;
   __threadfence_system();
+  __hip_atomic_store(&m->tag, n + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // alpha = |r|^2 / |Mhat p|^2, also shifted into the alpha history
@@ -63,7 +70,7 @@ __device__ __forceinline__ void state_alpha(CgState* st, double qq) {
 
 // End of an iteration: |r_{k+1}|^2, beta, the stopping test (FP64) or the
 // reliable-update request (mixed; it does not stop the recurrence).  Posts.
-__device__ __forceinline__ void state_beta(CgState* st, double rr_new, CgState* mbox, int ring) {
+__device__ __forceinline__ void state_beta(CgState* st, double rr_new, Mail* mbox, int ring) {
   st->iter += 1;
   if (!finite(rr_new)) {
     st->nan = 1;
@@ -91,7 +98,7 @@ __device__ __forceinline__ void state_beta(CgState* st, double rr_new, CgState* 
 
 // The iteration was already stopped: nothing to update, but the host still
 // expects one posted state per iteration.
-__device__ __forceinline__ void state_halted(CgState* st, CgState* mbox, int ring) {
+__device__ __forceinline__ void state_halted(CgState* st, Mail* mbox, int ring) {
   st->do_x = 0;
   st->do_p = 0;
   post(st, mbox, ring);
@@ -190,16 +197,16 @@ hipError_t launch_dot_re(const Geom& gv, int lg, SpF64 a, SpF64 b, double* parti
 // then sums: one workgroup alone cannot keep enough loads in flight.
 constexpr int kFoldSpan = 4096;
 constexpr int kFoldMin = 32768;
-hipError_t launch_fin_scalar(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s);
-// the sum of n partials of one right-hand side to *out (device or host-mapped memory)
-hipError_t launch_fin_sum(double* out, const double* partial, int n, double* fold, hipStream_t s);
+// the sums to out[r] (host-mapped memory)
+hipError_t launch_fin_sum(double* out, const double* partial, int n, int nr, double* fold, hipStream_t s);
+// starts a recurrence; the states' posts count on from seq
 hipError_t launch_fin_init(CgState* st, const double* partial, int n, int nr, double* fold, double tol, double delta,
-                           int max_iter, int mixed, CgState* mbox, int ring, hipStream_t s);
+                           int max_iter, int mixed, unsigned int seq, Mail* mbox, int ring, hipStream_t s);
 hipError_t launch_fin_alpha(CgState* st, const double* partial, int n, int nr, double* fold, hipStream_t s);
-hipError_t launch_fin_beta(CgState* st, const double* partial, int n, int nr, double* fold, CgState* mbox, int ring,
+hipError_t launch_fin_beta(CgState* st, const double* partial, int n, int nr, double* fold, Mail* mbox, int ring,
                            hipStream_t s);
 hipError_t launch_fin_ru(CgState* st, const double* partial, int n, int nr, double* fold, int restart, int nclear,
-                         CgState* mbox, int ring, hipStream_t s);
+                         Mail* mbox, int ring, hipStream_t s);
 // Iteration j of an n-iteration x cycle; p[0 .. n-1] are the cycle's direction buffers.
 hipError_t launch_xp_update_f64(const Geom& gv, int lg, const CgState* st, SpF64 x, const SpF64* p, int j, int n,
                                 SpF64 r, int block, hipStream_t s);
