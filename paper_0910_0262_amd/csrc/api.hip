@@ -314,10 +314,10 @@ void fuse_fin_alpha(const qcd_ctx* c, DslashOp& op) {
   op.fin_n = blocks_for(c->w->gv.Vh, c->block());  // the partials of the previous launch
   op.fin_nr = c->w->nr;
 }
-int k1_f64(qcd_ctx* c, int in, int out, bool dag, const CgState* st, bool fin_alpha = false) {
+int k1_ref(qcd_ctx* c, SpRef in, SpRef out, bool dag, const CgState* st, bool fin_alpha = false) {
   DslashOp op = base_op(c, 1);
-  op.in = c->ref64(in);
-  op.out = c->ref64(out);
+  op.in = in;
+  op.out = out;
   op.site_mode = 0;
   op.post = 1;
   op.cpost = ClovRef{CL_F64, c->clov_inv, nullptr};
@@ -328,13 +328,16 @@ int k1_f64(qcd_ctx* c, int in, int out, bool dag, const CgState* st, bool fin_al
   HIPCHK(launch_dslash(c->g, op, c->block(), c->stream));
   return QCD_OK;
 }
+int k1_f64(qcd_ctx* c, int in, int out, bool dag, const CgState* st, bool fin_alpha = false) {
+  return k1_ref(c, c->ref64(in), c->ref64(out), dag, st, fin_alpha);
+}
 // out_e = A_ee s_e - kappa^2 (g5) H_eo t_o, with epilogue
-int k2_f64(qcd_ctx* c, int site, int t, int out, bool dag, int epi, int y, double a, bool a_state,
+int k2_ref(qcd_ctx* c, SpRef site, SpRef t, SpRef out, bool dag, int epi, int y, double a, bool a_state,
            const CgState* st) {
   DslashOp op = base_op(c, 0);
-  op.in = c->ref64(t);
-  op.site = c->ref64(site);
-  op.out = c->ref64(out);
+  op.in = t;
+  op.site = site;
+  op.out = out;
   op.site_mode = 2;
   op.cpre = use_compact(c) && c->link_recon == 12 ? ClovRef{CL_F64C, c->clovc_e, nullptr}
                                                     : ClovRef{CL_F64, c->clov_par(0), nullptr};
@@ -347,6 +350,10 @@ int k2_f64(qcd_ctx* c, int site, int t, int out, bool dag, int epi, int y, doubl
   op.st = st;
   HIPCHK(launch_dslash(c->g, op, c->block(), c->stream));
   return QCD_OK;
+}
+int k2_f64(qcd_ctx* c, int site, int t, int out, bool dag, int epi, int y, double a, bool a_state,
+           const CgState* st) {
+  return k2_ref(c, c->ref64(site), c->ref64(t), c->ref64(out), dag, epi, y, a, a_state, st);
 }
 // mixed-precision k1 / k2 on binary16 spinors and links, FP32 arithmetic
 ClovRef mixed_clov(const qcd_ctx* c, bool inverse_odd) {
@@ -394,11 +401,11 @@ int k2_h(qcd_ctx* c, int site, int t, int out, bool dag, int epi, int y, bool a_
   return QCD_OK;
 }
 // full-lattice M (or M^dag) on parity p: out_p = A_pp in_p - kappa g5 H g5 in_(1-p), with epilogue
-int m_parity(qcd_ctx* c, int par, int in_site, int in_nbr, int out, bool dag, int epi, int y, double a) {
+int m_parity_ref(qcd_ctx* c, int par, int in_site, int in_nbr, SpRef out, bool dag, int epi, int y, double a) {
   DslashOp op = base_op(c, par);
   op.in = c->ref64(in_nbr);
   op.site = c->ref64(in_site);
-  op.out = c->ref64(out);
+  op.out = out;
   op.site_mode = 2;
   op.cpre = ClovRef{CL_F64, c->clov_par(par), nullptr};
   op.c = -c->kappa;
@@ -409,6 +416,10 @@ int m_parity(qcd_ctx* c, int par, int in_site, int in_nbr, int out, bool dag, in
   op.a = a;
   HIPCHK(launch_dslash(c->g, op, c->block(), c->stream));
   return QCD_OK;
+}
+
+int m_parity(qcd_ctx* c, int par, int in_site, int in_nbr, int out, bool dag, int epi, int y, double a) {
+  return m_parity_ref(c, par, in_site, in_nbr, c->ref64(out), dag, epi, y, a);
 }
 
 int nblocks(const qcd_ctx* c) { return blocks_for(c->w->gv.Vh, c->block()); }
@@ -1046,48 +1057,68 @@ int qcd_apply(qcd_ctx* c, int op, int prec, const void* in_dev, void* out_dev) {
     return fail(QCD_EINVAL, "the full-lattice operators are FP64 only");
   QCHK(need_clover(c));
   const Geom& g = c->g;
-  if (op == QCD_OP_M || op == QCD_OP_MDAG) {
-    const bool dag = op == QCD_OP_MDAG;
-    HIPCHK(launch_pack_spinor_full(g, (const double2*)in_dev, c->f64(V_IN_E), c->f64(V_IN_O), c->stream));
-    QCHK(m_parity(c, 0, V_IN_E, V_IN_O, V_OUT_E, dag, 0, 0, 0.0));
-    QCHK(m_parity(c, 1, V_IN_O, V_IN_E, V_OUT_O, dag, 0, 0, 0.0));
-    HIPCHK(launch_unpack_spinor_full(g, c->f64(V_OUT_E), c->f64(V_OUT_O), (double2*)out_dev, c->stream));
-    return QCD_OK;
-  }
-  HIPCHK(launch_pack_spinor_cb(g, (const double2*)in_dev, c->f64(V_IN_E), c->stream));
   const bool first = op == QCD_OP_MHAT || op == QCD_OP_MHATDAGMHAT;
   const bool second = op == QCD_OP_MHATDAG || op == QCD_OP_MHATDAGMHAT;
-  if (prec == QCD_FP64) {
-    int cur = V_IN_E;
+  const bool full = op == QCD_OP_M || op == QCD_OP_MDAG;
+  if (prec == QCD_MIXED) {
+    HIPCHK(launch_pack_half_cb(g, (const double2*)in_dev, c->h(H_IN), c->stream));
+    int cur = H_IN;
     if (first) {
-      QCHK(k1_f64(c, cur, V_T, false, nullptr));
-      QCHK(k2_f64(c, cur, V_T, V_OUT_E, false, 0, 0, 0.0, false, nullptr));
-      cur = V_OUT_E;
+      QCHK(k1_h(c, cur, H_T, false, nullptr));
+      QCHK(k2_h(c, cur, H_T, H_OUT, false, 0, 0, false, nullptr));
+      cur = H_OUT;
     }
     if (second) {
-      const int dst = cur == V_OUT_E ? V_AUX : V_OUT_E;
-      QCHK(k1_f64(c, cur, V_T, true, nullptr));
-      QCHK(k2_f64(c, cur, V_T, dst, true, 0, 0, 0.0, false, nullptr));
+      const int dst = cur == H_OUT ? H_Q : H_OUT;
+      QCHK(k1_h(c, cur, H_T, true, nullptr));
+      QCHK(k2_h(c, cur, H_T, dst, true, 0, 0, false, nullptr));
       cur = dst;
     }
-    HIPCHK(launch_unpack_spinor_cb(g, c->f64(cur), (double2*)out_dev, c->stream));
+    HIPCHK(launch_unpack_half_cb(g, c->h(cur), (double2*)out_dev, c->stream));
     return QCD_OK;
   }
-  HIPCHK(launch_convert(c->w->gv, c->ref64(V_IN_E), c->refh(H_IN), c->block(), c->stream));
-  int cur = H_IN;
-  if (first) {
-    QCHK(k1_h(c, cur, H_T, false, nullptr));
-    QCHK(k2_h(c, cur, H_T, H_OUT, false, 0, 0, false, nullptr));
-    cur = H_OUT;
+  // On small lattices the stencils read and write the caller's arrays: a
+  // launch costs about 5 us there whatever it does (M at 4^4 17.6 -> 6.7 us
+  // in one launch instead of four, Mhat at 8x8x16x16 20.6 -> 15.7 us).  On
+  // larger ones the neighbour reads want the packed layout, and only the
+  // result goes out directly (Mhat at 32^3x64 819 -> 765 us).  Arrays that
+  // share memory go through the packed input on every lattice.
+  const uintptr_t bytes = (uintptr_t)(full ? g.V : g.Vh) * 12 * sizeof(double2);
+  const uintptr_t in_at = (uintptr_t)in_dev, out_at = (uintptr_t)out_dev;
+  const bool apart = in_at + bytes <= out_at || out_at + bytes <= in_at;
+  const bool direct = apart && stencil_reads_user(g, c->small_grid, c->block());
+  if (full) {
+    const bool dag = op == QCD_OP_MDAG;
+    if (direct) {
+      DslashOp d = base_op(c, 0);
+      d.in = d.site = SpRef{SP_USER_FULL, (void*)in_dev, nullptr};
+      d.out = SpRef{SP_USER_FULL, out_dev, nullptr};
+      d.site_mode = 2;
+      d.cpre = ClovRef{CL_F64, c->clov_par(0), nullptr};
+      d.c = -c->kappa;
+      d.g5in = dag;
+      d.g5out = dag;
+      HIPCHK(launch_dslash(g, d, c->block(), c->stream));
+      return QCD_OK;
+    }
+    HIPCHK(launch_pack_spinor_full(g, (const double2*)in_dev, c->f64(V_IN_E), c->f64(V_IN_O), c->stream));
+    const SpRef out = SpRef{SP_USER_FULL, out_dev, nullptr};
+    QCHK(m_parity_ref(c, 0, V_IN_E, V_IN_O, out, dag, 0, 0, 0.0));
+    return m_parity_ref(c, 1, V_IN_O, V_IN_E, out, dag, 0, 0, 0.0);
   }
-  if (second) {
-    const int dst = cur == H_OUT ? H_Q : H_OUT;
-    QCHK(k1_h(c, cur, H_T, true, nullptr));
-    QCHK(k2_h(c, cur, H_T, dst, true, 0, 0, false, nullptr));
+  if (!direct) HIPCHK(launch_pack_spinor_cb(g, (const double2*)in_dev, c->f64(V_IN_E), c->stream));
+  SpRef cur = direct ? SpRef{SP_USER, (void*)in_dev, nullptr} : c->ref64(V_IN_E);
+  const SpRef end = SpRef{SP_USER, out_dev, nullptr}, t = c->ref64(V_T);
+  if (first) {
+    const SpRef dst = second ? c->ref64(V_AUX) : end;
+    QCHK(k1_ref(c, cur, t, false, nullptr));
+    QCHK(k2_ref(c, cur, t, dst, false, 0, 0, 0.0, false, nullptr));
     cur = dst;
   }
-  HIPCHK(launch_convert(c->w->gv, c->refh(cur), c->ref64(V_OUT_E), c->block(), c->stream));
-  HIPCHK(launch_unpack_spinor_cb(g, c->f64(V_OUT_E), (double2*)out_dev, c->stream));
+  if (second) {
+    QCHK(k1_ref(c, cur, t, true, nullptr));
+    QCHK(k2_ref(c, cur, t, end, true, 0, 0, 0.0, false, nullptr));
+  }
   return QCD_OK;
 }
 

@@ -672,6 +672,37 @@ hipError_t launch_zero(const Geom& g, SpRef x, int block, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The caller's checkerboard array straight to binary16 and back (through an
+// FP64 field, as two passes each way, mixed Mhat^dag Mhat at 32^3x64 took 606
+// instead of 480 us).
+__global__ void __launch_bounds__(256) pack_half_cb_k(int n, const double2* __restrict__ user, SpH f) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  Spinor<float> v;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const double2 d = user[(size_t)i * 12 + k];
+    v.v[k / 3][k % 3] = {float(d.x), float(d.y)};
+  }
+  store(f, i, v);
+}
+__global__ void __launch_bounds__(256) unpack_half_cb_k(int n, SpH f, double2* __restrict__ user) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  Spinor<double> v;
+  load(f, i, v);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) user[(size_t)i * 12 + k] = make_double2(v.v[k / 3][k % 3].re, v.v[k / 3][k % 3].im);
+}
+hipError_t launch_pack_half_cb(const Geom& g, const double2* user, SpH f, hipStream_t s) {
+  hipLaunchKernelGGL(pack_half_cb_k, dim3(blocks_for(g.Vh, 256)), dim3(256), 0, s, g.Vh, user, f);
+  return hipGetLastError();
+}
+hipError_t launch_unpack_half_cb(const Geom& g, SpH f, double2* user, hipStream_t s) {
+  hipLaunchKernelGGL(unpack_half_cb_k, dim3(blocks_for(g.Vh, 256)), dim3(256), 0, s, g.Vh, f, user);
+  return hipGetLastError();
+}
+
 // Reference encoder for checking: user complex128 [n][12] -> codes [n][3] x 8 binary16, scale [n]
 __global__ void encode_half_k(int n, const double2* __restrict__ user, uint4* __restrict__ codes,
                               float* __restrict__ scale) {

@@ -272,6 +272,8 @@ dslash_kernel(A a) {
         for (int k = 0; k < 3; ++k) yv.v[s][k] = yv.v[s][k] + al * acc.v[s][k];
       store(a.out, e, yv);
       nrm = site_norm2(yv);
+    } else if constexpr (std::is_same<decltype(a.out), SpUser>::value) {
+      store(a.out, element_of(a.out, 2 * i + (x[0] & 1)), acc);
     } else {
       store(a.out, e, acc);
       if (a.epi == 1) nrm = site_norm2(acc);
@@ -304,6 +306,14 @@ __device__ __forceinline__ void load_half(const SpF64& f, int i, Cx<R> v[6]) {
     v[j] = {R(d.x), R(d.y)};
   }
 }
+template <int H, typename R>
+__device__ __forceinline__ void load_half(const SpUser& f, int i, Cx<R> v[6]) {
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const double2 d = f.p[(size_t)i * 12 + 6 * H + j];
+    v[j] = {R(d.x), R(d.y)};
+  }
+}
 // binary16 chunk k holds complex components 4k .. 4k + 3: half 0 is chunk 0
 // and the first 8 bytes of chunk 1, half 1 the last 8 bytes of chunk 1 and
 // chunk 2.
@@ -331,6 +341,11 @@ __device__ __forceinline__ void store_half(const SpF64& f, int i, const Cx<R> v[
     const nt_d2 w = {double(v[j].re), double(v[j].im)};
     __builtin_nontemporal_store(w, (nt_d2*)(f.p + sp64_at(6 * H + j, i)));
   }
+}
+template <int H, typename R>
+__device__ __forceinline__ void store_half(const SpUser& f, int i, const Cx<R> v[6], float) {
+#pragma unroll
+  for (int j = 0; j < 6; ++j) f.p[(size_t)i * 12 + 6 * H + j] = make_double2(double(v[j].re), double(v[j].im));
 }
 // m: the site's max |component| over both halves, as the one-work-item encoder takes it
 template <int H, typename R>
@@ -371,17 +386,17 @@ __device__ __forceinline__ void hop_one(const A& a, int i, const int x[4], Spino
     y[MU] = (x[MU] + 1 == g.X[MU]) ? 0 : x[MU] + 1;
   else
     y[MU] = (x[MU] == 0 ? g.X[MU] : x[MU]) - 1;
-  const int n = lex(y, g) >> 1;
+  const int l = lex(y, g), n = l >> 1;
   Spinor<R> p;
   Mat<R> u;
-  load_raw(a.in, n, p);
+  load_raw(a.in, element_of(a.in, l), p);
   if (S < 0)
     load_link(a.U, MU, a.par_out, i, u);
   else
     load_link(a.U, MU, 1 - a.par_out, n, u);
   if constexpr (G5IN) neg_lower(p);
   R sc = R(1);
-  if constexpr (scaled) sc = R(scale_of(a.in, n));
+  if constexpr (scaled) sc = R(scale_of(a.in, n));  // scaled fields are never the caller's
   if constexpr (MU == 3) sc = (g.tb < 0 && x[3] == (S < 0 ? g.X[3] - 1 : 0)) ? -sc : sc;
   Half<R> h, uh;
   if constexpr (scaled)
@@ -443,7 +458,7 @@ __device__ __forceinline__ void pair_hops(const A& a, int i, int lane, PairLds<R
 // Chiral half H of a site from the sum v of all its hops: hop factor, site
 // term, clover, epilogue value; returns the half's max |component|.
 template <int H, typename R, int SITE, bool POST, class A>
-__device__ __forceinline__ float finish_half(const A& a, int i, Cx<R> v[6]) {
+__device__ __forceinline__ float finish_half(const A& a, int i, int l, Cx<R> v[6]) {
   const R c = H == 0 ? R(a.c) : (a.g5out ? R(-a.c) : R(a.c));
   constexpr bool FUSED_CL = sizeof(R) == 4;
   if constexpr (POST && SITE == 0) {
@@ -453,7 +468,7 @@ __device__ __forceinline__ float finish_half(const A& a, int i, Cx<R> v[6]) {
     for (int j = 0; j < 6; ++j) v[j] = c * v[j];
     if constexpr (SITE != 0) {
       Cx<R> sv[6];
-      load_half<H>(a.site, i, sv);
+      load_half<H>(a.site, element_of(a.site, l), sv);
       if constexpr (SITE == 2) {
         if constexpr (CloverCompact<decltype(a.cpre)>::value) {
           CBlock<R> blk;
@@ -475,7 +490,7 @@ __device__ __forceinline__ float finish_half(const A& a, int i, Cx<R> v[6]) {
   }
   if (a.epi == 2) {
     Cx<R> yv[6];
-    load_half<H>(a.y, i, yv);
+    load_half<H>(a.y, element_of(a.y, l), yv);
     const R al = a.a_from_state ? R(-a.st->alpha) : R(a.a);
 #pragma unroll
     for (int j = 0; j < 6; ++j) v[j] = yv[j] + al * v[j];
@@ -489,7 +504,7 @@ template <int H, typename R, int SITE, bool POST, class A>
 __device__ __forceinline__ void pair_finish(const A& a, int i, int lane, PairLds<R>& L, Cx<R> v[6]) {
 #pragma unroll
   for (int j = 0; j < 6; ++j) v[j] = v[j] + L.part[H][j][lane];
-  L.m[H][lane] = finish_half<H, R, SITE, POST>(a, i, v);
+  L.m[H][lane] = finish_half<H, R, SITE, POST>(a, i, 2 * i, v);
 }
 
 template <typename R, int SITE, bool POST, bool G5IN, class A>
@@ -566,10 +581,28 @@ __global__ void __launch_bounds__(256) dslash_quad_kernel(A a) {
   else if (a.st != nullptr && a.st->halt)
     return;
   __shared__ QuadLds<R> L;
-  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  int blk = xcd_block(blockIdx.x, gridDim.x);
+  // on the caller's whole-lattice arrays a launch does both parities, the even
+  // one's workgroups first; the clover field holds the odd sites' blocks after
+  // the even ones'
+  constexpr bool user_full = SITE == 2 && std::is_same<decltype(a.in), SpUser>::value;
+  if constexpr (user_full) {
+    const int half = gridDim.x >> 1;
+    if (blk >= half) {
+      blk -= half;
+      a.par_out = 1;
+      a.cpre.p += (size_t)36 * a.cpre.stride;
+    }
+  }
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int i = blk * 64 + lane;
   const bool live = i < a.g.Vh;
+  int l = 2 * i;  // lexicographic index (or, where no caller's array is written, one whose half is i)
+  if constexpr (std::is_same<decltype(a.out), SpUser>::value) {
+    int x[4];
+    cb_coords(i, a.par_out, a.g, x);
+    l += x[0] & 1;
+  }
   if (live) {
     Spinor<R> acc;
     if (w == 0)
@@ -592,18 +625,18 @@ __global__ void __launch_bounds__(256) dslash_quad_kernel(A a) {
     for (int j = 0; j < 6; ++j)
       v[j] = ((L.part[0][w][j][lane] + L.part[1][w][j][lane]) + L.part[2][w][j][lane]) + L.part[3][w][j][lane];
     if (w == 0)
-      L.m[0][lane] = finish_half<0, R, SITE, POST>(a, i, v);
+      L.m[0][lane] = finish_half<0, R, SITE, POST>(a, i, l, v);
     else
-      L.m[1][lane] = finish_half<1, R, SITE, POST>(a, i, v);
+      L.m[1][lane] = finish_half<1, R, SITE, POST>(a, i, l, v);
   }
   __syncthreads();
   double nrm = 0.0;
   if (live && w < 2) {
     const float m = fmaxf(L.m[0][lane], L.m[1][lane]);
     if (w == 0)
-      store_half<0>(a.out, i, v, m);
+      store_half<0>(a.out, element_of(a.out, l), v, m);
     else
-      store_half<1>(a.out, i, v, m);
+      store_half<1>(a.out, element_of(a.out, l), v, m);
     if (a.epi >= 1) {
 #pragma unroll
       for (int j = 0; j < 6; ++j) nrm += double(v[j].re) * double(v[j].re) + double(v[j].im) * double(v[j].im);
@@ -621,6 +654,8 @@ template <>
 SpF32 sp_of<SpF32>(const SpRef& r, int stride) { return SpF32{(float4*)r.p, stride}; }
 template <>
 SpH sp_of<SpH>(const SpRef& r, int stride) { return SpH{(uint4*)r.p, r.s, stride}; }
+template <>
+SpUser sp_of<SpUser>(const SpRef& r, int) { return SpUser{(double2*)r.p, r.kind == SP_USER_FULL}; }
 template <>
 SpNone sp_of<SpNone>(const SpRef&, int) { return SpNone{}; }
 
@@ -660,6 +695,12 @@ LinkH18 lk_of<LinkH18>(const void* p, int stride) {
 // wavefront per SIMD (256 CUs x 4 SIMDs x 64 lanes), and the single-source
 // stencils take two wavefronts per 64 sites instead
 constexpr int kSmallVh = 256 * 4 * 64;
+bool stencil_reads_user(const Geom& g, int small_grid, int block) {
+  return g.Vh <= kSmallVh && small_grid == 2 && block == 64;
+}
+static bool small_direct(const Geom& g, const DslashOp& op, int block) {
+  return op.lg == 0 && stencil_reads_user(g, op.small_grid, block);
+}
 
 template <typename R, class SIn, class SSite, class SOut, class LK, class CPre, class CPost, int SITE, bool POST,
           bool G5IN>
@@ -695,6 +736,23 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
   a.fin_n = op.fin_n;
   a.fin_nr = op.fin_nr;
   const int nb = blocks_for(g.Vh << op.lg, block);
+  // the four-wavefront kernel takes the caller's arrays everywhere, the one
+  // with a work-item per site for the result (and the others never)
+  constexpr bool user_in = std::is_same<SIn, SpUser>::value || std::is_same<SSite, SpUser>::value;
+  constexpr bool user_out = std::is_same<SOut, SpUser>::value;
+  if constexpr (user_out && !user_in) {
+    if (!small_direct(g, op, block)) {
+      if (op.lg > 0 || op.epi != 0) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, false, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (user_in || user_out) {
+    constexpr bool both = user_in && SITE == 2 && std::is_same<SIn, SpUser>::value;  // the whole lattice
+    if (!small_direct(g, op, block) || both != (op.in.kind == SP_USER_FULL)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dslash_quad_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(both ? 2 * nb : nb), dim3(256), 0, s, a);
+    return hipGetLastError();
+  } else {
   constexpr bool multi_only = std::is_same<LK, LinkH18>::value;  // 18-entry links serve the multi-source kernels
   if (op.lg > 0)
     hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, true, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
@@ -702,11 +760,12 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
     return hipErrorInvalidValue;
   else if (g.Vh <= kSmallVh && op.small_grid == 1 && block == 64)
     hipLaunchKernelGGL((dslash_pair_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(nb), dim3(128), 0, s, a);
-  else if (g.Vh <= kSmallVh && op.small_grid == 2 && block == 64)
+  else if (small_direct(g, op, block))
     hipLaunchKernelGGL((dslash_quad_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(nb), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, false, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
   return hipGetLastError();
+  }
 }
 
 template <typename R, class SIn, class SSite, class SOut, class LK, class CPre, class CPost, int SITE, bool POST>
@@ -715,9 +774,44 @@ static hipError_t run(const Geom& g, const DslashOp& op, int block, hipStream_t 
   return run_g5<R, SIn, SSite, SOut, LK, CPre, CPost, SITE, POST, false>(g, op, block, s);
 }
 
+bool is_user(const SpRef& r) { return r.kind == SP_USER || r.kind == SP_USER_FULL; }
+// FP64 stencils on the caller's arrays: k1 from one, k2 with its site term
+// and / or its result in one, and the full-lattice operator.
+template <int NC, class CL>
+static hipError_t run_user_k2(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
+  using L = LinkF64<NC>;
+  if (is_user(op.site) && is_user(op.out))
+    return run_g5<double, SpF64, SpUser, SpUser, L, CL, CloverNone, 2, false, false>(g, op, block, s);
+  if (is_user(op.site))
+    return run_g5<double, SpF64, SpUser, SpF64, L, CL, CloverNone, 2, false, false>(g, op, block, s);
+  return run_g5<double, SpF64, SpF64, SpUser, L, CL, CloverNone, 2, false, false>(g, op, block, s);
+}
+template <int NC>
+static hipError_t run_user(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
+  using L = LinkF64<NC>;
+  if (op.epi != 0) return hipErrorInvalidValue;
+  if (op.site_mode == 0 && op.post && is_user(op.in) && !is_user(op.out))
+    return run<double, SpUser, SpNone, SpF64, L, CloverNone, CloverF64, 0, true>(g, op, block, s);
+  if (op.site_mode != 2 || op.post) return hipErrorInvalidValue;
+  if (is_user(op.in)) {
+    if (!is_user(op.site) || !is_user(op.out) || op.cpre.kind != CL_F64) return hipErrorInvalidValue;
+    return run<double, SpUser, SpUser, SpUser, L, CloverF64, CloverNone, 2, false>(g, op, block, s);
+  }
+  if (op.g5in) {  // the full-lattice dagger on packed fields
+    if (is_user(op.site) || op.cpre.kind != CL_F64) return hipErrorInvalidValue;
+    return run_g5<double, SpF64, SpF64, SpUser, L, CloverF64, CloverNone, 2, false, true>(g, op, block, s);
+  }
+  if constexpr (NC == 6) {
+    if (op.cpre.kind == CL_F64C) return run_user_k2<NC, CloverF64C>(g, op, block, s);
+  }
+  if (op.cpre.kind != CL_F64) return hipErrorInvalidValue;
+  return run_user_k2<NC, CloverF64>(g, op, block, s);
+}
+
 template <int NC>
 static hipError_t run_f64(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
   using L = LinkF64<NC>;
+  if (is_user(op.in) || is_user(op.site) || is_user(op.out)) return run_user<NC>(g, op, block, s);
   if (op.site_mode == 0 && op.post)
     return run<double, SpF64, SpNone, SpF64, L, CloverNone, CloverF64, 0, true>(g, op, block, s);
   if (op.site_mode == 2 && !op.post) {
@@ -745,7 +839,7 @@ static hipError_t run_mixed(const Geom& g, const DslashOp& op, int block, hipStr
 }
 
 hipError_t launch_dslash(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
-  if (op.in.kind == SP_F64) {
+  if (op.in.kind == SP_F64 || is_user(op.in)) {
     if (op.link_kind == LK_F64_12) return run_f64<6>(g, op, block, s);
     if (op.link_kind == LK_F64_18) return run_f64<9>(g, op, block, s);
     return hipErrorInvalidValue;

@@ -376,6 +376,13 @@ __device__ __forceinline__ size_t sp64_at(int k, size_t i) { return (((i >> 6) *
 // p + 64 k, a 32-bit index (the host keeps 48 i below 2^32); the per-site
 // scales are a plain array.
 __device__ __forceinline__ int sph_at(int i) { return ((i >> 6) * 3 << 6) + (i & 63); }
+// The caller's site-major array, component k of site i at p[12 i + k]: one
+// checkerboard, or (full) the whole lattice in lexicographic order.  The
+// small-lattice stencils read and write it directly.
+struct SpUser {
+  double2* p;
+  int full;
+};
 struct SpF32 {   // 6 chunks of float4 (two complex each), 96 B / site
   float4* p;
   int stride;
@@ -405,12 +412,27 @@ __device__ __forceinline__ void store(const SpF64& f, int i, const Spinor<R>& v)
     __builtin_nontemporal_store(w, (nt_d2*)(f.p + sp64_at(k, i)));
   }
 }
+// (Plain stores: a lane's 16-byte pieces of a line meet in the L2.)
+template <typename R>
+__device__ __forceinline__ void store(const SpUser& f, int i, const Spinor<R>& v) {
+#pragma unroll
+  for (int k = 0; k < 12; ++k)
+    f.p[(size_t)i * 12 + k] = make_double2(double(v.v[k / 3][k % 3].re), double(v.v[k / 3][k % 3].im));
+}
 // Site-local spinor read once per kernel (the k2 site term, the epilogue's y).
 template <typename R>
 __device__ __forceinline__ void load_once(const SpF64& f, int i, Spinor<R>& v) {
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
     const double2 d = ld_stream(f.p + sp64_at(k, i));
+    v.v[k / 3][k % 3] = {R(d.x), R(d.y)};
+  }
+}
+template <typename R>
+__device__ __forceinline__ void load_once(const SpUser& f, int i, Spinor<R>& v) {
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const double2 d = f.p[(size_t)i * 12 + k];
     v.v[k / 3][k % 3] = {R(d.x), R(d.y)};
   }
 }
@@ -447,6 +469,14 @@ __device__ __forceinline__ void load_raw(const SpF64& f, int i, Spinor<R>& v) {
   load(f, i, v);
 }
 template <typename R>
+__device__ __forceinline__ void load_raw(const SpUser& f, int i, Spinor<R>& v) {
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const double2 d = f.p[(size_t)i * 12 + k];
+    v.v[k / 3][k % 3] = {R(d.x), R(d.y)};
+  }
+}
+template <typename R>
 __device__ __forceinline__ void load_raw(const SpH& f, int i, Spinor<R>& v) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -460,6 +490,12 @@ __device__ __forceinline__ void load_raw(const SpH& f, int i, Spinor<R>& v) {
 }
 __device__ __forceinline__ float scale_of(const SpH& f, int i) { return *elem(f.s, 0, i); }
 __device__ __forceinline__ float scale_of(const SpF64&, int) { return 1.0f; }
+__device__ __forceinline__ float scale_of(const SpUser&, int) { return 1.0f; }
+// Element of the site with lexicographic index l: its checkerboard index, but
+// for a caller's whole-lattice array.
+template <class F>
+__device__ __forceinline__ int element_of(const F&, int l) { return l >> 1; }
+__device__ __forceinline__ int element_of(const SpUser& f, int l) { return f.full ? l : l >> 1; }
 
 template <typename R>
 __device__ __forceinline__ void load(const SpH& f, int i, Spinor<R>& v) {

@@ -104,7 +104,10 @@ __device__ __forceinline__ void state_halted(CgState* st, Mail* mbox, int ring) 
   post(st, mbox, ring);
 }
 
-enum SpKind { SP_NONE = 0, SP_F64 = 1, SP_F32 = 2, SP_H = 3 };
+// SP_USER, SP_USER_FULL: the caller's site-major array, one checkerboard or the
+// whole lattice.  A stencil from a whole-lattice array to another does both
+// parities in one launch (par_out 0, cpre the even sites' clover).
+enum SpKind { SP_NONE = 0, SP_F64 = 1, SP_F32 = 2, SP_H = 3, SP_USER = 4, SP_USER_FULL = 5 };
 struct SpRef {
   int kind;
   void* p;
@@ -158,6 +161,8 @@ struct DslashOp {
 inline int blocks_for(int n, int block) { return (n + block - 1) / block; }
 
 // ---- dslash.hip
+// Whether the single-source stencils run the small-lattice form that takes the caller's arrays
+bool stencil_reads_user(const Geom& g, int small_grid, int block);
 hipError_t launch_dslash(const Geom& g, const DslashOp& op, int block, hipStream_t s);
 hipError_t launch_clover_apply(const Geom& g, int lg, SpF64 in, SpF64 out, const double2* clov, hipStream_t s);
 
@@ -219,6 +224,10 @@ hipError_t launch_ru_accum(const Geom& gv, int lg, const CgState* st, SpF64 xhi,
                            int block, hipStream_t s);
 hipError_t launch_convert(const Geom& g, SpRef src, SpRef dst, int block, hipStream_t s);
 hipError_t launch_zero(const Geom& g, SpRef x, int block, hipStream_t s);
+// the caller's checkerboard array to the binary16 field and back, as a
+// conversion through an FP64 field would
+hipError_t launch_pack_half_cb(const Geom& g, const double2* user, SpH f, hipStream_t s);
+hipError_t launch_unpack_half_cb(const Geom& g, SpH f, double2* user, hipStream_t s);
 hipError_t launch_encode_half(int n, const double2* user, uint4* codes, float* scale, hipStream_t s);
 hipError_t launch_stream_copy(const uint4* src, uint4* dst, uint64_t n16, hipStream_t s);
 
