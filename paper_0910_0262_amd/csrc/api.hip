@@ -100,8 +100,9 @@ struct qcd_ctx {
   uint4* uh18 = nullptr;        // all nine entries in binary16, for the multi-source kernels
   double2* clov = nullptr;      // A, both parities: [par][36][stride]
   double2* clov_inv = nullptr;  // A_oo^{-1}: [36][stride]
-  float4* clov32_e = nullptr;   // A_ee in FP32
+  float4* clov32_e = nullptr;   // A_ee in FP32 (only with the FP32 clover option)
   float4* clovinv32_o = nullptr;
+  bool clov32_ok = false;
   uint4* clovh_e = nullptr;     // A_ee in binary16 + scale
   float2* clovh_es = nullptr;
   uint4* clovinvh_o = nullptr;
@@ -119,7 +120,7 @@ struct qcd_ctx {
   int wm_lg_alloc = -1;  // right-hand sides (log2) wm was allocated for
   hipStream_t cap = nullptr;    // private stream used only to capture graphs
   hipGraphExec_t iter_graph[2][4] = {};  // one CG iteration: [FP64, mixed][position in the x cycle]
-  int* status = nullptr;
+  int* status = nullptr;       // device address of status_host
   int* status_host = nullptr;  // host-mapped
   double2* xi = nullptr;       // clover-force Xi: [par][6][kXiChunks][stride]
   double2* gint = nullptr;     // force accumulator: [mu][par][9][stride]
@@ -261,7 +262,6 @@ void free_ctx(qcd_ctx* c) {
   f(c->clovhc_es);
   free_work(c->w1);
   free_work(c->wm);
-  f(c->status);
   f(c->xi);
   f(c->gint);
   f(c->md_partial);
@@ -903,7 +903,6 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   A(&c->clovc_e, 26 * S * sizeof(double2));
   A(&c->clovhc_e, 6 * S * sizeof(uint4) + S * sizeof(uint2));
   A(&c->clovhc_es, S * sizeof(float2));
-  A(&c->status, 2 * sizeof(int));
   A(&c->md_partial, (md_link_partials(g) + md_link_partials(g) / kFoldSpan + 1) * sizeof(double));
   if (rc == QCD_OK) rc = alloc_work(g, c->w1, 0, true);
   // one host-mapped block: the actions, the norms, the clover status
@@ -915,6 +914,7 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   c->norm_host = c->act_host + 3 * kActRing;
   c->norm_dev = c->act_dev + 3 * kActRing;
   c->status_host = (int*)(c->act_host + n_sums);
+  c->status = (int*)(c->act_dev + n_sums);
   if (rc == QCD_OK && hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
     rc = fail(QCD_EHIP, "hipStreamCreate failed");
   if (rc != QCD_OK) {
@@ -949,6 +949,8 @@ int qcd_set_params(qcd_ctx* c, double kappa, double csw, int t_boundary) {
   return QCD_OK;
 }
 
+static int clover_copy32(qcd_ctx* c);
+
 int qcd_set_option(qcd_ctx* c, int option, int value) {
   QCHK(check_ctx(c));
   drop_graphs(c);
@@ -960,7 +962,8 @@ int qcd_set_option(qcd_ctx* c, int option, int value) {
     case QCD_OPT_MIXED_CLOVER:
       if (value != 16 && value != 32) return fail(QCD_EINVAL, "mixed clover storage must be 16 or 32");
       c->mixed_clover = value;
-      return QCD_OK;
+      // the copies of a clover term that is there already
+      return c->clover_ready && value == 32 && !c->clov32_ok ? clover_copy32(c) : QCD_OK;
     case QCD_OPT_BLOCK:
       if (value != 0 && (value < 64 || value > 256 || value % 64 != 0))
         return fail(QCD_EINVAL, "block size must be 0 or a multiple of 64 in [64, 256]");
@@ -1008,18 +1011,27 @@ int qcd_store_gauge(qcd_ctx* c, void* U_dev) {
   return QCD_OK;
 }
 
-static int invert_clover(qcd_ctx* c) {
-  HIPCHK(hipMemsetAsync(c->status, 0, 2 * sizeof(int), c->stream));
-  HIPCHK(launch_clover_invert(c->g, c->clov, c->clov_inv, c->clov32_e, c->clovinv32_o, c->clovh_e, c->clovh_es,
-                              c->clovinvh_o, c->clovinvh_os, c->logdet, c->status, c->stream));
-  HIPCHK(launch_clover_compact(c->g, c->clov, c->clovc_e, c->clovhc_e, c->clovhc_es, c->status + 1, c->stream));
-  HIPCHK(hipMemcpyAsync(c->status_host, c->status, 2 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
+static CloverOut clover_out(qcd_ctx* c) {
+  c->status_host[0] = c->status_host[1] = 0;
+  return CloverOut{c->clov_inv, c->clovh_e,  c->clovh_es,  c->clovinvh_o, c->clovinvh_os,
+                   c->clovc_e,  c->clovhc_e, c->clovhc_es, c->logdet,     c->status};
+}
+
+// The FP32 copies, where the FP32 clover option asks for them.
+static int clover_copy32(qcd_ctx* c) {
+  if (c->mixed_clover == 32)
+    HIPCHK(launch_clover_copy32(c->g, c->clov, c->clov_inv, c->clov32_e, c->clovinv32_o, c->stream));
+  c->clov32_ok = c->mixed_clover == 32;
+  return QCD_OK;
+}
+
+// After the kernels of a new clover term: waits for them and looks at their status.
+static int clover_done(qcd_ctx* c) {
+  c->clover_ready = false;
+  QCHK(clover_copy32(c));
   HIPCHK(hipStreamSynchronize(c->stream));
   c->compact_ok = c->status_host[1] == 0;
-  if (*c->status_host != 0) {
-    c->clover_ready = false;
-    return fail(QCD_ECLOVER, "an odd-site clover block is not positive definite");
-  }
+  if (c->status_host[0] != 0) return fail(QCD_ECLOVER, "an odd-site clover block is not positive definite");
   c->clover_ready = true;
   return QCD_OK;
 }
@@ -1027,8 +1039,8 @@ static int invert_clover(qcd_ctx* c) {
 int qcd_build_clover(qcd_ctx* c) {
   QCHK(check_ctx(c));
   QCHK(need_gauge(c));
-  HIPCHK(launch_clover_build(c->g, c->u18, c->kappa, c->csw, c->clov, c->stream));
-  return invert_clover(c);
+  HIPCHK(launch_clover_build(c->g, c->u18, c->kappa, c->csw, c->clov, clover_out(c), c->stream));
+  return clover_done(c);
 }
 
 int qcd_load_clover(qcd_ctx* c, const double* A_dev) {
@@ -1036,7 +1048,8 @@ int qcd_load_clover(qcd_ctx* c, const double* A_dev) {
   if (!A_dev) return fail(QCD_EINVAL, "null clover pointer");
   QCHK(need_gauge(c));
   HIPCHK(launch_pack_clover(c->g, (const double2*)A_dev, c->clov, c->stream));
-  return invert_clover(c);
+  HIPCHK(launch_clover_invert(c->g, c->clov, clover_out(c), c->stream));
+  return clover_done(c);
 }
 
 int qcd_get_clover(qcd_ctx* c, double* A_dev, double* Ainv_dev) {

@@ -232,13 +232,28 @@ hipError_t launch_encode_half(int n, const double2* user, uint4* codes, float* s
 hipError_t launch_stream_copy(const uint4* src, uint4* dst, uint64_t n16, hipStream_t s);
 
 // ---- clover.hip
+// What is derived from the clover term A: A_oo^{-1} and ln det A (odd sites),
+// the binary16 copies of A_ee and A_oo^{-1} with their per-block scales, and
+// the compact copies of A_ee.  status[0] is set (in host-mapped memory) if an
+// odd block is not positive definite, status[1] if a loaded A_ee does not have
+// the compact form.
+struct CloverOut {
+  double2* inv;
+  uint4* h_e;
+  float2* h_es;
+  uint4* hinv_o;
+  float2* hinv_os;
+  double2* c64;
+  uint4* ch;
+  float2* chs;
+  double* logdet;
+  int* status;
+};
 hipError_t launch_clover_build(const Geom& g, const double2* u18, double kappa, double csw, double2* clov,
-                               hipStream_t s);
-hipError_t launch_clover_compact(const Geom& g, const double2* clov_e, double2* c64, uint4* ch, float2* chs,
-                                 int* status, hipStream_t s);
-hipError_t launch_clover_invert(const Geom& g, const double2* clov, double2* clov_inv, float4* clov32_e,
-                                float4* clovinv32_o, uint4* clovh_e, float2* clovh_es, uint4* clovinvh_o,
-                                float2* clovinvh_os, double* logdet, int* status, hipStream_t s);
+                               const CloverOut& o, hipStream_t s);
+hipError_t launch_clover_invert(const Geom& g, const double2* clov, const CloverOut& o, hipStream_t s);
+hipError_t launch_clover_copy32(const Geom& g, const double2* clov, const double2* inv, float4* e32, float4* inv32,
+                                hipStream_t s);
 
 // ---- force.hip
 // Where a force pass puts G (dS/dRe U + i dS/dIm U): any of the accumulator
