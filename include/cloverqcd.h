@@ -216,14 +216,13 @@ int qcd_solve(qcd_ctx *ctx, const qcd_solver_params *params, const void *b_dev, 
  * right-hand sides are interleaved site by site in the library's fields, so
  * each link and clover block is read once per site for all of them.  This
  * is the multi-source workload of the paper's application (section 1), whose
- * kernels are bound by memory bandwidth (section 4).  Internally n_rhs is
- * rounded up to a power of two with zero right-hand sides, which converge at
- * once.  b_dev, x_dev: complex128 [n_rhs][V][4][3], not overlapping.  stats:
+ * kernels are bound by memory bandwidth (section 4).
+ * b_dev, x_dev: complex128 [n_rhs][V][4][3], not overlapping.  stats:
  * NULL or n_rhs entries; iters and reliable_updates count the joint
  * iterations (the largest over the right-hand sides), seconds the whole call,
  * flops each right-hand side's share, bytes the call's algorithmic bytes over
  * n_rhs.  The first call with a given n_rhs allocates the interleaved work
- * vectors (about 12 x n_rhs' spinor fields, n_rhs' = the rounded count); they
+ * vectors (about 12 x n_rhs' spinor fields, n_rhs' = the next power of two); they
  * are kept for later calls with as many or fewer right-hand sides.
  * QCD_EINVAL if V/2 (rounded up to a multiple of 64) x n_rhs' x 48 reaches
  * 2^32 (the kernels address a field element with a 32-bit byte offset).  QCD_ENOCONV if any right-hand side

@@ -58,12 +58,12 @@ constexpr int kActRing = 64;
 
 }  // namespace
 
-// Solver work set: vectors, partial sums and CG states for nr = 1 << lg
-// right-hand sides interleaved site by site (element (cb << lg) | r).  The
-// context's single-source set (lg = 0) also serves the operators, the force
+// Solver work set: vectors, partial sums and CG states for nr right-hand
+// sides interleaved site by site (element cb * nr + r).  The context's
+// single-source set (nr = 1) also serves the operators, the force
 // and the trajectory; a second set is allocated for multi-source solves.
 struct Work {
-  int lg = 0, nr = 1;
+  int nr = 1;
   Geom gv;  // Vh and stride of all right-hand sides together (for the BLAS kernels)
   double2* vec[NSLOT] = {};
   uint4* hv[NHSLOT] = {};
@@ -97,7 +97,7 @@ struct qcd_ctx {
   double2* u18 = nullptr;
   double2* u12 = nullptr;
   uint2* uh = nullptr;
-  uint4* uh18 = nullptr;        // all nine entries in binary16, for the multi-source kernels
+  LinkRow* uh18 = nullptr;      // all nine entries in binary16, for the multi-source kernels
   double2* clov = nullptr;      // A, both parities: [par][36][stride]
   double2* clov_inv = nullptr;  // A_oo^{-1}: [36][stride]
   float4* clov32_e = nullptr;   // A_ee in FP32 (only with the FP32 clover option)
@@ -117,7 +117,7 @@ struct qcd_ctx {
   Work w1;          // single source (operators, solve, force, trajectory)
   Work wm;          // multi-source solves
   Work* w = &w1;    // the set the solver drivers use
-  int wm_lg_alloc = -1;  // right-hand sides (log2) wm was allocated for
+  int wm_alloc = 0;  // right-hand sides wm was allocated for
   hipStream_t cap = nullptr;    // private stream used only to capture graphs
   hipGraphExec_t iter_graph[2][4] = {};  // one CG iteration: [FP64, mixed][position in the x cycle]
   int* status = nullptr;       // device address of status_host
@@ -184,14 +184,13 @@ void free_work(Work& w) {
   w = Work();
 }
 
-// Allocate a work set for 1 << lg right-hand sides; with all_slots the
+// Allocate a work set for nr right-hand sides; with all_slots the
 // vectors of the operators and the force too, otherwise the solver's only.
-int alloc_work(const Geom& g, Work& w, int lg, bool all_slots) {
-  w.lg = lg;
-  w.nr = 1 << lg;
+int alloc_work(const Geom& g, Work& w, int nr, bool all_slots) {
+  w.nr = nr;
   w.gv = g;
-  w.gv.Vh = g.Vh << lg;
-  w.gv.stride = g.stride << lg;
+  w.gv.Vh = g.Vh * nr;
+  w.gv.stride = g.stride * nr;
   const size_t S = (size_t)w.gv.stride;
   int rc = QCD_OK;
   auto A = [&](auto** p, size_t bytes) {
@@ -299,7 +298,7 @@ DslashOp base_op(const qcd_ctx* c, int par_out) {
   op.links = c->links64();
   op.c = 1.0;
   op.partial = c->w->partial;
-  op.lg = c->w->lg;
+  op.nr = c->w->nr;
   op.small_grid = c->small_grid;
   return op;
 }
@@ -366,8 +365,8 @@ ClovRef mixed_clov(const qcd_ctx* c, bool inverse_odd) {
 // right-hand side, where bytes decide; all nine entries for several, where
 // the rebuild's instructions would be repeated by every right-hand side
 void mixed_links(const qcd_ctx* c, DslashOp& op) {
-  op.link_kind = c->w->lg > 0 ? LK_H18 : LK_H12;
-  op.links = c->w->lg > 0 ? (const void*)c->uh18 : (const void*)c->uh;
+  op.link_kind = c->w->nr > 1 ? LK_H18 : LK_H12;
+  op.links = c->w->nr > 1 ? (const void*)c->uh18 : (const void*)c->uh;
 }
 int k1_h(qcd_ctx* c, int in, int out, bool dag, const CgState* st, bool fin_alpha = false) {
   DslashOp op = base_op(c, 1);
@@ -430,7 +429,7 @@ double* fold_area(const qcd_ctx* c) {
 
 // |x|^2 of each right-hand side of an FP64 vector to norm_host[16 slot + r]
 int post_norm2(qcd_ctx* c, int s, int slot) {
-  HIPCHK(launch_norm2(c->w->gv, c->w->lg, c->ref64(s), c->w->partial, c->block(), c->stream));
+  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->ref64(s), c->w->partial, c->block(), c->stream));
   HIPCHK(launch_fin_sum(c->norm_dev + 16 * slot, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
   return QCD_OK;
 }
@@ -555,7 +554,7 @@ int recompute_residual(qcd_ctx* c, int restart, CgState* posted, int nclear = 0)
 
 // Starts the recurrence; its first state is posted with *tag.
 int init_recurrence(qcd_ctx* c, double tol, double delta, int max_iter, int mixed, unsigned int* tag) {
-  HIPCHK(launch_norm2(c->w->gv, c->w->lg, c->ref64(V_RHS), c->w->partial, c->block(), c->stream));
+  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->ref64(V_RHS), c->w->partial, c->block(), c->stream));
   HIPCHK(launch_fin_init(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), tol, delta, max_iter, mixed,
                          c->w->post_ctr, c->w->mbox_dev, kRing, c->stream));
   *tag = next_tag(c);
@@ -594,7 +593,7 @@ int launch_iter(qcd_ctx* c, bool mixed, int j) {
     HIPCHK(launch_fin_beta(c->w->st, c->w->partial, nb, c->w->nr, fold_area(c), c->w->mbox_dev, kRing, c->stream));
     SpF64 p[4];
     for (int m = 0; m < n; ++m) p[m] = c->f64(qcd_ctx::pslot(m));
-    HIPCHK(launch_xp_update_f64(c->w->gv, c->w->lg, c->w->st, c->f64(V_X), p, j, n, c->f64(V_R), kXpBlock, c->stream));
+    HIPCHK(launch_xp_update_f64(c->w->gv, c->w->nr, c->w->st, c->f64(V_X), p, j, n, c->f64(V_R), kXpBlock, c->stream));
   } else {
     const int pj = qcd_ctx::hpslot(j);
     QCHK(k1_h(c, pj, H_T, false, c->w->st));
@@ -605,7 +604,7 @@ int launch_iter(qcd_ctx* c, bool mixed, int j) {
     HIPCHK(launch_fin_beta(c->w->st, c->w->partial, nb, c->w->nr, fold_area(c), c->w->mbox_dev, kRing, c->stream));
     SpH p[4];
     for (int m = 0; m < n; ++m) p[m] = c->h(qcd_ctx::hpslot(m));
-    HIPCHK(launch_xp_update_h(c->w->gv, c->w->lg, c->w->st, c->f32(), p, j, n, c->h(H_R), kXpBlock, c->stream));
+    HIPCHK(launch_xp_update_h(c->w->gv, c->w->nr, c->w->st, c->f32(), p, j, n, c->h(H_R), kXpBlock, c->stream));
   }
   return QCD_OK;
 }
@@ -646,7 +645,7 @@ int capture_iter(qcd_ctx* c, bool mixed, int j) {
 // Iteration pp.seq of the recurrence is the (pp.seq mod x_defer)-th of its x cycle.
 int enqueue_iter(qcd_ctx* c, Pipe& pp, bool mixed) {
   const int j = (int)(pp.seq % c->x_defer);
-  if (c->use_graph && c->w->lg == 0) {
+  if (c->use_graph && c->w->nr == 1) {
     QCHK(capture_iter(c, mixed, j));
     HIPCHK(hipGraphLaunch(c->iter_graph[mixed ? 1 : 0][j], c->stream));
   } else {
@@ -685,7 +684,7 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
     QCHK(recompute_residual(c, 1, &s));
     cnt.mdagm += 1;
     if (s.nan) return fail(QCD_ENAN, "non-finite residual of the starting guess");
-    HIPCHK(launch_p_restart_f64(c->w->gv, c->w->lg, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
+    HIPCHK(launch_p_restart_f64(c->w->gv, c->w->nr, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
   } else {
     HIPCHK(launch_zero(c->w->gv, c->ref64(V_X), B, c->stream));
     HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->ref64(V_R), B, c->stream));
@@ -710,7 +709,7 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
     if (s.nan) return fail(QCD_ENAN, "non-finite residual in FP64 CG");
     if (s.done || restarts >= 8) break;
     ++restarts;
-    HIPCHK(launch_p_restart_f64(c->w->gv, c->w->lg, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
+    HIPCHK(launch_p_restart_f64(c->w->gv, c->w->nr, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
     pp = Pipe();
   }
   cnt.iters += s.iter;
@@ -727,7 +726,7 @@ int fold_x(qcd_ctx* c, const Pipe& pp) {
   const int q = (int)(pp.seq % c->x_defer);
   SpH p[4];
   for (int m = 0; m < q; ++m) p[m] = c->h(qcd_ctx::hpslot(m));
-  HIPCHK(launch_ru_accum(c->w->gv, c->w->lg, c->w->st, c->f64(V_X), c->f32(), p, q, c->block(), c->stream));
+  HIPCHK(launch_ru_accum(c->w->gv, c->w->nr, c->w->st, c->f64(V_X), c->f32(), p, q, c->block(), c->stream));
   return q;
 }
 
@@ -890,7 +889,7 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   A(&c->u18, 8 * 9 * S * sizeof(double2));
   A(&c->u12, 8 * 6 * S * sizeof(double2));
   A(&c->uh, 8 * 3 * S * sizeof(uint2));
-  A(&c->uh18, 8 * 2 * S * sizeof(uint4) + 8 * S * sizeof(unsigned int));
+  A(&c->uh18, 8 * 3 * S * sizeof(LinkRow));
   A(&c->clov, 2 * 36 * S * sizeof(double2));
   A(&c->clov_inv, 36 * S * sizeof(double2));
   A(&c->clov32_e, 18 * S * sizeof(float4));
@@ -904,7 +903,7 @@ int qcd_create(const int dims[4], int device, uintptr_t hip_stream, qcd_ctx** ou
   A(&c->clovhc_e, 6 * S * sizeof(uint4) + S * sizeof(uint2));
   A(&c->clovhc_es, S * sizeof(float2));
   A(&c->md_partial, (md_link_partials(g) + md_link_partials(g) / kFoldSpan + 1) * sizeof(double));
-  if (rc == QCD_OK) rc = alloc_work(g, c->w1, 0, true);
+  if (rc == QCD_OK) rc = alloc_work(g, c->w1, 1, true);
   // one host-mapped block: the actions, the norms, the clover status
   constexpr size_t n_sums = 3 * kActRing + 4 * 16;
   if (rc == QCD_OK && (hipHostMalloc((void**)&c->act_host, n_sums * sizeof(double) + 2 * sizeof(int),
@@ -1146,24 +1145,27 @@ struct WorkGuard {
   ~WorkGuard() { c->w = &c->w1; }
 };
 
-// Make the multi-source work set hold 1 << lg right-hand sides.
-int use_multi(qcd_ctx* c, int lg) {
+// Make the multi-source work set hold n right-hand sides.  Memory and the
+// limit on the volume are those of the next power of two, so that requests
+// for a few more or fewer reuse one allocation.
+int use_multi(qcd_ctx* c, int n) {
+  int room = 1;
+  while (room < n) room *= 2;
   // the stencils address a chunk element with a 32-bit byte offset (16-byte
   // elements; 48 bytes per element of the tiled binary16 fields)
-  if (((long long)c->g.stride << lg) * 48 >= (1LL << 32))
+  if ((long long)c->g.stride * room * 48 >= (1LL << 32))
     return fail(QCD_EINVAL, "too many interleaved right-hand sides for this lattice volume");
-  if (c->wm.st == nullptr || c->wm_lg_alloc < lg) {
+  if (c->wm.st == nullptr || c->wm_alloc < room) {
     free_work(c->wm);
-    c->wm_lg_alloc = -1;
-    QCHK(alloc_work(c->g, c->wm, lg, false));
-    c->wm_lg_alloc = lg;
+    c->wm_alloc = 0;
+    QCHK(alloc_work(c->g, c->wm, room, false));
+    c->wm_alloc = room;
   }
   Work& w = c->wm;
-  w.lg = lg;
-  w.nr = 1 << lg;
+  w.nr = n;
   w.gv = c->g;
-  w.gv.Vh = c->g.Vh << lg;
-  w.gv.stride = c->g.stride << lg;
+  w.gv.Vh = c->g.Vh * n;
+  w.gv.stride = c->g.stride * n;
   return QCD_OK;
 }
 
@@ -1173,7 +1175,7 @@ int solve_packed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
   const Geom& g = c->g;
   const int B = c->block(), nb = nblocks(c), nr = c->w->nr;
   // bhat = b_e + kappa H_eo A_oo^{-1} b_o; rhs = Mhat^dag bhat
-  HIPCHK(launch_clover_apply(g, c->w->lg, c->f64(V_B_O), c->f64(V_T), c->clov_inv, c->stream));
+  HIPCHK(launch_clover_apply(g, c->w->nr, c->f64(V_B_O), c->f64(V_T), c->clov_inv, c->stream));
   {
     DslashOp op = base_op(c, 0);
     op.in = c->ref64(V_T);
@@ -1251,16 +1253,14 @@ int qcd_solve_multi(qcd_ctx* c, const qcd_solver_params* p, int n_rhs, const voi
   if (b_dev == x_dev) return fail(QCD_EINVAL, "b and x must not overlap");
   QCHK(need_clover(c));
   const auto t0 = std::chrono::steady_clock::now();
-  int lg = 0;
-  while ((1 << lg) < n_rhs) ++lg;
   // a set allocated for more right-hand sides serves fewer (its buffers are larger)
-  QCHK(use_multi(c, lg));
+  QCHK(use_multi(c, n_rhs));
   Work& w = c->wm;
   WorkGuard wg(c, &w);
-  HIPCHK(launch_pack_spinor_multi(c->g, lg, n_rhs, (const double2*)b_dev, c->f64(V_B_E), c->f64(V_B_O), c->stream));
+  HIPCHK(launch_pack_spinor_multi(c->g, n_rhs, (const double2*)b_dev, c->f64(V_B_E), c->f64(V_B_O), c->stream));
   CgCounters cnt;
   QCHK(solve_packed(c, p, cnt));
-  HIPCHK(launch_unpack_spinor_multi(c->g, lg, n_rhs, c->f64(V_X), c->f64(V_OUT_O), (double2*)x_dev, c->stream));
+  HIPCHK(launch_unpack_spinor_multi(c->g, n_rhs, c->f64(V_X), c->f64(V_OUT_O), (double2*)x_dev, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return solve_report(c, p, n_rhs, cnt, stats, t0);
 }
@@ -1289,7 +1289,7 @@ static int force_core(qcd_ctx* c, const qcd_solver_params* p, int slot, CgCounte
   if (rc != QCD_OK) return rc;
   *conv_rc = c->w->st_host->rr_hi <= c->w->st_host->stop2 ? QCD_OK : QCD_ENOCONV;
   // S = Re phi^dag X
-  HIPCHK(launch_dot_re(c->w->gv, c->w->lg, c->f64(V_RHS), c->f64(V_X), c->w->partial, c->block(), c->stream));
+  HIPCHK(launch_dot_re(c->w->gv, c->w->nr, c->f64(V_RHS), c->f64(V_X), c->w->partial, c->block(), c->stream));
   HIPCHK(launch_fin_sum(c->act_dev + 3 * slot, c->w->partial, nb, 1, fold_area(c), c->stream));
   // Z = A_oo^{-1} H_oe X; Y = Mhat X; W = A_oo^{-1} g5 H_oe g5 Y
   QCHK(k1_f64(c, V_X, V_Z, false, nullptr));
@@ -1661,9 +1661,7 @@ int qcd_time_stencil(qcd_ctx* c, int prec, int n, double* ms) {
 int qcd_time_stencil_multi(qcd_ctx* c, int prec, int n_rhs, int n, double* ms) {
   QCHK(check_time_args(c, prec, n, ms));
   if (n_rhs < 1 || n_rhs > QCD_MAX_RHS) return fail(QCD_EINVAL, "n_rhs must lie in [1, 16]");
-  int lg = 0;
-  while ((1 << lg) < n_rhs) ++lg;
-  QCHK(use_multi(c, lg));
+  QCHK(use_multi(c, n_rhs));
   WorkGuard wg(c, &c->wm);
   const int f[4] = {V_P, V_T, V_Q, V_AUX}, h[4] = {H_P, H_T, H_Q, H_R};
   return time_stencil_impl(c, prec, n, ms, f, h);

@@ -57,46 +57,44 @@ __global__ void unpack_spinor_cb_k(int n, SpF64 f, double2* __restrict__ user) {
   for (int k = 0; k < 12; ++k) user[(size_t)i * 12 + k] = v[k];
 }
 
-// n right-hand sides [n][V][12] -> interleaved fields, element (cb << lg) | r;
-// one thread per (site, rhs slot), slots r >= n are zero.
-__global__ void pack_spinor_multi_k(Geom g, int lg, int n, const double2* __restrict__ user, SpF64 e, SpF64 o) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ((size_t)g.V << lg)) return;
-  const int r = (int)(t & ((1u << lg) - 1)), i = (int)(t >> lg);
+// n right-hand sides [n][V][12] <-> interleaved fields; one thread per (site,
+// right-hand side).
+__global__ void pack_spinor_multi_k(Geom g, RhsDiv d, const double2* __restrict__ user, SpF64 e, SpF64 o) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  int r;
+  const int i = rhs_split(t, d, r);
+  if (i >= g.V) return;
   int x[4];
   lex_coords(i, g, x);
   const SpF64 f = parity_of(x) ? o : e;
-  const size_t v = ((size_t)(i >> 1) << lg) | r;
+  const size_t v = (size_t)(i >> 1) * d.n + r;
   double2 w[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) w[k] = r < n ? user[((size_t)r * g.V + i) * 12 + k] : make_double2(0.0, 0.0);
+  for (int k = 0; k < 12; ++k) w[k] = user[((size_t)r * g.V + i) * 12 + k];
 #pragma unroll
   for (int k = 0; k < 12; ++k) f.p[sp64_at(k, v)] = w[k];
 }
-__global__ void unpack_spinor_multi_k(Geom g, int lg, int n, SpF64 e, SpF64 o, double2* __restrict__ user) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ((size_t)g.V << lg)) return;
-  const int r = (int)(t & ((1u << lg) - 1)), i = (int)(t >> lg);
-  if (r >= n) return;
+__global__ void unpack_spinor_multi_k(Geom g, RhsDiv d, SpF64 e, SpF64 o, double2* __restrict__ user) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  int r;
+  const int i = rhs_split(t, d, r);
+  if (i >= g.V) return;
   int x[4];
   lex_coords(i, g, x);
   const SpF64 f = parity_of(x) ? o : e;
-  const size_t v = ((size_t)(i >> 1) << lg) | r;
+  const size_t v = (size_t)(i >> 1) * d.n + r;
   double2 w[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) w[k] = f.p[sp64_at(k, v)];
 #pragma unroll
   for (int k = 0; k < 12; ++k) user[((size_t)r * g.V + i) * 12 + k] = w[k];
 }
-hipError_t launch_pack_spinor_multi(const Geom& g, int lg, int n, const double2* user, SpF64 e, SpF64 o,
-                                    hipStream_t s) {
-  const size_t nt = (size_t)g.V << lg;
-  hipLaunchKernelGGL(pack_spinor_multi_k, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, g, lg, n, user, e, o);
+hipError_t launch_pack_spinor_multi(const Geom& g, int n, const double2* user, SpF64 e, SpF64 o, hipStream_t s) {
+  hipLaunchKernelGGL(pack_spinor_multi_k, dim3(blocks_for(g.V * n, 256)), dim3(256), 0, s, g, rhs_div(n), user, e, o);
   return hipGetLastError();
 }
-hipError_t launch_unpack_spinor_multi(const Geom& g, int lg, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s) {
-  const size_t nt = (size_t)g.V << lg;
-  hipLaunchKernelGGL(unpack_spinor_multi_k, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, g, lg, n, e, o,
+hipError_t launch_unpack_spinor_multi(const Geom& g, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s) {
+  hipLaunchKernelGGL(unpack_spinor_multi_k, dim3(blocks_for(g.V * n, 256)), dim3(256), 0, s, g, rhs_div(n), e, o,
                      user);
   return hipGetLastError();
 }
@@ -216,7 +214,7 @@ hipError_t launch_unpack_clover(const Geom& g, const double2* clov, double2* use
 // ------------------------------------------------------------------ reductions
 // gv: Vh and stride of all interleaved right-hand sides together.
 template <class F>
-__global__ void __launch_bounds__(256) norm2_k(Geom gv, int lg, F x, double* partial) {
+__global__ void __launch_bounds__(256) norm2_k(Geom gv, RhsDiv d, F x, double* partial) {
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   const int i = blk * blockDim.x + threadIdx.x;
   double n = 0.0;
@@ -225,9 +223,9 @@ __global__ void __launch_bounds__(256) norm2_k(Geom gv, int lg, F x, double* par
     load(x, i, v);
     n = site_norm2(v);
   }
-  block_sum_store_seg(n, partial, blk, gridDim.x, lg);
+  block_sum_store_seg(n, partial, blk, gridDim.x, d);
 }
-__global__ void __launch_bounds__(256) dot_re_k(Geom gv, int lg, SpF64 a, SpF64 b, double* partial) {
+__global__ void __launch_bounds__(256) dot_re_k(Geom gv, RhsDiv d, SpF64 a, SpF64 b, double* partial) {
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   const int i = blk * blockDim.x + threadIdx.x;
   double n = 0.0;
@@ -238,22 +236,22 @@ __global__ void __launch_bounds__(256) dot_re_k(Geom gv, int lg, SpF64 a, SpF64 
       n += u.x * v.x + u.y * v.y;
     }
   }
-  block_sum_store_seg(n, partial, blk, gridDim.x, lg);
+  block_sum_store_seg(n, partial, blk, gridDim.x, d);
 }
-hipError_t launch_norm2(const Geom& gv, int lg, SpRef x, double* partial, int block, hipStream_t s) {
+hipError_t launch_norm2(const Geom& gv, int nr, SpRef x, double* partial, int block, hipStream_t s) {
   const int nb = blocks_for(gv.Vh, block);
   if (x.kind == SP_F64)
-    hipLaunchKernelGGL(norm2_k<SpF64>, dim3(nb), dim3(block), 0, s, gv, lg, SpF64{(double2*)x.p, gv.stride}, partial);
+    hipLaunchKernelGGL(norm2_k<SpF64>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpF64{(double2*)x.p, gv.stride}, partial);
   else if (x.kind == SP_F32)
-    hipLaunchKernelGGL(norm2_k<SpF32>, dim3(nb), dim3(block), 0, s, gv, lg, SpF32{(float4*)x.p, gv.stride}, partial);
+    hipLaunchKernelGGL(norm2_k<SpF32>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpF32{(float4*)x.p, gv.stride}, partial);
   else if (x.kind == SP_H)
-    hipLaunchKernelGGL(norm2_k<SpH>, dim3(nb), dim3(block), 0, s, gv, lg, SpH{(uint4*)x.p, x.s, gv.stride}, partial);
+    hipLaunchKernelGGL(norm2_k<SpH>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpH{(uint4*)x.p, x.s, gv.stride}, partial);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
-hipError_t launch_dot_re(const Geom& gv, int lg, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s) {
-  hipLaunchKernelGGL(dot_re_k, dim3(blocks_for(gv.Vh, block)), dim3(block), 0, s, gv, lg, a, b, partial);
+hipError_t launch_dot_re(const Geom& gv, int nr, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s) {
+  hipLaunchKernelGGL(dot_re_k, dim3(blocks_for(gv.Vh, block)), dim3(block), 0, s, gv, rhs_div(nr), a, b, partial);
   return hipGetLastError();
 }
 
@@ -403,17 +401,19 @@ hipError_t launch_fin_ru(CgState* st, const double* partial, int n, int nr, doub
 // `pout`; x takes sum_{m <= j} ah[m] p_{j-m} at the end of the cycle (`last`)
 // or when the recurrence stops at this iteration (do_p == 0), so every
 // direction reaches x once.  ah[] is the state's alpha history, newest first.
-// Element i belongs to right-hand side i & ((1 << lg) - 1) and uses its state.
+// Element i belongs to right-hand side i mod d.n and uses its state.
 template <class Sp>
 struct Older {
   Sp p[3];
 };
 
 template <int NOLD>
-__global__ void __launch_bounds__(256) xp_update_f64_k(Geom g, int lg, const CgState* st, SpF64 x, SpF64 pc,
+__global__ void __launch_bounds__(256) xp_update_f64_k(Geom g, RhsDiv d, const CgState* st, SpF64 x, SpF64 pc,
                                                        Older<SpF64> old, SpF64 pout, SpF64 r, int last) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  st += i & ((1 << lg) - 1);
+  int rhs;
+  (void)rhs_split(i, d, rhs);
+  st += rhs;
   if (!st->do_x) return;
   if (i >= g.Vh) return;
   const double be = st->beta;
@@ -460,9 +460,11 @@ __global__ void __launch_bounds__(256) xp_update_f64_k(Geom g, int lg, const CgS
   }
 }
 // CG restart (beta is zero after one): p = r where the recurrence continues.
-__global__ void __launch_bounds__(256) p_restart_f64_k(Geom g, int lg, const CgState* st, SpF64 p, SpF64 r) {
+__global__ void __launch_bounds__(256) p_restart_f64_k(Geom g, RhsDiv d, const CgState* st, SpF64 p, SpF64 r) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  st += i & ((1 << lg) - 1);
+  int rhs;
+  (void)rhs_split(i, d, rhs);
+  st += rhs;
   if (!st->do_p) return;
   if (i >= g.Vh) return;
   Spinor<double> v;
@@ -472,10 +474,12 @@ __global__ void __launch_bounds__(256) p_restart_f64_k(Geom g, int lg, const CgS
 // mixed: the same cycle with x in FP32 and the directions in binary16
 // (re-encoded per site when written).
 template <int NOLD>
-__global__ void __launch_bounds__(256) xp_update_h_k(Geom g, int lg, const CgState* st, SpF32 x, SpH pc,
+__global__ void __launch_bounds__(256) xp_update_h_k(Geom g, RhsDiv d, const CgState* st, SpF32 x, SpH pc,
                                                      Older<SpH> old, SpH pout, SpH r, int last) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  st += i & ((1 << lg) - 1);
+  int rhs;
+  (void)rhs_split(i, d, rhs);
+  st += rhs;
   if (!st->do_x) return;
   if (i >= g.Vh) return;
   const float be = float(st->beta);
@@ -520,11 +524,13 @@ __global__ void __launch_bounds__(256) xp_update_h_k(Geom g, int lg, const CgSta
 // (pend.p[m] = p_{q-1-m} with weight ah[m], m < NQ, for right-hand sides whose
 // last iteration ran); x_lo = 0.  The sum is taken in FP64.
 template <int NQ>
-__global__ void __launch_bounds__(256) ru_accum_k(Geom g, int lg, const CgState* st, SpF64 xhi, SpF32 xlo,
+__global__ void __launch_bounds__(256) ru_accum_k(Geom g, RhsDiv d, const CgState* st, SpF64 xhi, SpF32 xlo,
                                                   Older<SpH> pend) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.Vh) return;
-  st += i & ((1 << lg) - 1);
+  int rhs;
+  (void)rhs_split(i, d, rhs);
+  st += rhs;
   Spinor<double> a, b;
   load(xhi, i, a);
   load(xlo, i, b);
@@ -562,7 +568,7 @@ Older<Sp> older_of(const Sp* p, int j) {
 }
 }  // namespace
 
-hipError_t launch_xp_update_f64(const Geom& gv, int lg, const CgState* st, SpF64 x, const SpF64* p, int j, int n,
+hipError_t launch_xp_update_f64(const Geom& gv, int nr, const CgState* st, SpF64 x, const SpF64* p, int j, int n,
                                 SpF64 r, int block, hipStream_t s) {
   if (n < 1 || n > 4 || j < 0 || j >= n) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(gv.Vh, block));
@@ -570,19 +576,19 @@ hipError_t launch_xp_update_f64(const Geom& gv, int lg, const CgState* st, SpF64
   const SpF64 pout = p[(j + 1) % n];
   const int last = j == n - 1;
   switch (j) {
-    case 0: hipLaunchKernelGGL(xp_update_f64_k<0>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    case 1: hipLaunchKernelGGL(xp_update_f64_k<1>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    case 2: hipLaunchKernelGGL(xp_update_f64_k<2>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    default: hipLaunchKernelGGL(xp_update_f64_k<3>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
+    case 0: hipLaunchKernelGGL(xp_update_f64_k<0>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    case 1: hipLaunchKernelGGL(xp_update_f64_k<1>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    case 2: hipLaunchKernelGGL(xp_update_f64_k<2>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    default: hipLaunchKernelGGL(xp_update_f64_k<3>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
   }
   return hipGetLastError();
 }
-hipError_t launch_p_restart_f64(const Geom& gv, int lg, const CgState* st, SpF64 p, SpF64 r, int block,
+hipError_t launch_p_restart_f64(const Geom& gv, int nr, const CgState* st, SpF64 p, SpF64 r, int block,
                                 hipStream_t s) {
-  hipLaunchKernelGGL(p_restart_f64_k, dim3(blocks_for(gv.Vh, block)), dim3(block), 0, s, gv, lg, st, p, r);
+  hipLaunchKernelGGL(p_restart_f64_k, dim3(blocks_for(gv.Vh, block)), dim3(block), 0, s, gv, rhs_div(nr), st, p, r);
   return hipGetLastError();
 }
-hipError_t launch_xp_update_h(const Geom& gv, int lg, const CgState* st, SpF32 x, const SpH* p, int j, int n, SpH r,
+hipError_t launch_xp_update_h(const Geom& gv, int nr, const CgState* st, SpF32 x, const SpH* p, int j, int n, SpH r,
                               int block, hipStream_t s) {
   if (n < 1 || n > 4 || j < 0 || j >= n) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(gv.Vh, block));
@@ -590,24 +596,24 @@ hipError_t launch_xp_update_h(const Geom& gv, int lg, const CgState* st, SpF32 x
   const SpH pout = p[(j + 1) % n];
   const int last = j == n - 1;
   switch (j) {
-    case 0: hipLaunchKernelGGL(xp_update_h_k<0>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    case 1: hipLaunchKernelGGL(xp_update_h_k<1>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    case 2: hipLaunchKernelGGL(xp_update_h_k<2>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
-    default: hipLaunchKernelGGL(xp_update_h_k<3>, grid, dim3(block), 0, s, gv, lg, st, x, p[j], o, pout, r, last); break;
+    case 0: hipLaunchKernelGGL(xp_update_h_k<0>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    case 1: hipLaunchKernelGGL(xp_update_h_k<1>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    case 2: hipLaunchKernelGGL(xp_update_h_k<2>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
+    default: hipLaunchKernelGGL(xp_update_h_k<3>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, x, p[j], o, pout, r, last); break;
   }
   return hipGetLastError();
 }
-hipError_t launch_ru_accum(const Geom& gv, int lg, const CgState* st, SpF64 xhi, SpF32 xlo, const SpH* p, int q,
+hipError_t launch_ru_accum(const Geom& gv, int nr, const CgState* st, SpF64 xhi, SpF32 xlo, const SpH* p, int q,
                            int block, hipStream_t s) {
   if (q < 0 || q > 3) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(gv.Vh, block));
   Older<SpH> pend{};
   for (int m = 0; m < q; ++m) pend.p[m] = p[q - 1 - m];
   switch (q) {
-    case 0: hipLaunchKernelGGL(ru_accum_k<0>, grid, dim3(block), 0, s, gv, lg, st, xhi, xlo, pend); break;
-    case 1: hipLaunchKernelGGL(ru_accum_k<1>, grid, dim3(block), 0, s, gv, lg, st, xhi, xlo, pend); break;
-    case 2: hipLaunchKernelGGL(ru_accum_k<2>, grid, dim3(block), 0, s, gv, lg, st, xhi, xlo, pend); break;
-    default: hipLaunchKernelGGL(ru_accum_k<3>, grid, dim3(block), 0, s, gv, lg, st, xhi, xlo, pend); break;
+    case 0: hipLaunchKernelGGL(ru_accum_k<0>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, xhi, xlo, pend); break;
+    case 1: hipLaunchKernelGGL(ru_accum_k<1>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, xhi, xlo, pend); break;
+    case 2: hipLaunchKernelGGL(ru_accum_k<2>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, xhi, xlo, pend); break;
+    default: hipLaunchKernelGGL(ru_accum_k<3>, grid, dim3(block), 0, s, gv, rhs_div(nr), st, xhi, xlo, pend); break;
   }
   return hipGetLastError();
 }

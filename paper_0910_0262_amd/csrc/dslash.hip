@@ -22,6 +22,10 @@ namespace qcd {
 
 struct SpNone {};
 
+// Right-hand sides of a dslash_kernel: one; a power of two; any number; a power of two from 4 on, binary16
+// (hops on the matrix cores).
+enum { ONE_SOURCE, MULTI_POW2, MULTI_ANY, MULTI_MFMA };
+
 template <class SIn, class SSite, class SOut, class LK, class CPre, class CPost>
 struct DArgs {
   Geom g;
@@ -40,7 +44,7 @@ struct DArgs {
   int g5in, g5out;
   const CgState* st;
   double* partial;
-  int lg;  // log2 of the number of interleaved right-hand sides (MULTI kernels)
+  RhsDiv rhs;  // interleaved right-hand sides
   // MULTI site order: z-tiles of 1 << tile_lg planes, t inside a tile
   int tile_lg, plane;  // plane = (Lx / 2) Ly checkerboard sites per z-t plane
   double inv_plane, inv_t;
@@ -101,8 +105,8 @@ __device__ __forceinline__ void scale_half(Half<R>& h, R f) {
 // the projected half spinor.  No branch may split this block: with a
 // branch the FP64 kernel runs out of registers and spills.
 // i: checkerboard site (links, clover); r: right-hand side (MULTI: spinor
-// element (cb << lg) | r, otherwise cb).
-template <int MU, bool G5IN, bool MULTI, bool FUSED, bool SCALED_ACC, typename R, class A>
+// element cb * rhs.n + r, otherwise cb).
+template <int MU, bool G5IN, int SOURCES, bool FUSED, bool SCALED_ACC, typename R, class A>
 __device__ __forceinline__ void hop_dir(const A& a, int i, int r, const int x[4], Spinor<R>& acc, R cu, R cl) {
   using SIn = decltype(a.in);
   constexpr bool scaled = SpinorScale<SIn>::scaled;
@@ -112,7 +116,9 @@ __device__ __forceinline__ void hop_dir(const A& a, int i, int r, const int x[4]
   const int nf = lex(y, g) >> 1;
   y[MU] = (x[MU] == 0 ? g.X[MU] : x[MU]) - 1;
   const int nb = lex(y, g) >> 1;
-  const int ef = MULTI ? ((nf << a.lg) | r) : nf, eb = MULTI ? ((nb << a.lg) | r) : nb;
+  constexpr bool POW2 = SOURCES != MULTI_ANY;
+  const int ef = SOURCES == ONE_SOURCE ? nf : rhs_element<POW2>(nf, r, a.rhs);
+  const int eb = SOURCES == ONE_SOURCE ? nb : rhs_element<POW2>(nb, r, a.rhs);
   Spinor<R> pf, pb;
   Mat<R> uf, ub;
   load_raw(a.in, ef, pf);
@@ -155,6 +161,129 @@ __device__ __forceinline__ void hop_dir(const A& a, int i, int r, const int x[4]
     accumulate<MU, +1>(acc, uh);
 }
 
+// ------------------------------------------------------------------ hops on the matrix cores
+// The multi-source binary16 stencil is bound by vector-instruction issue while
+// its fields fit the caches (at 16^4 with 8 sources; 79 % of all issue slots
+// even at 32^3x64, where memory is the bound), and the projection and the
+// 3x3 product are most of it.  v_mfma_f32_4x4x4_16b_f16 does sixteen
+// independent 4x4x4 products: a block is four right-hand sides of one site
+// (lanes 4 b .. 4 b + 3), lane i holds row i of the link (row 3 repeats row 2
+// and its result is dropped) and, as column i, its own spinor, whose upper and
+// lower spins both enter the product, the projection's +-1 and +-i folded
+// into the link's operand.  The sum runs over (spin, colour, re / im) = 12 real
+// products in three instructions, for each real component of the half spinor:
+// products of binary16 values are exact in FP32 and are summed there (root
+// mean square error 3.7e-8 of the result; with FMA chains 5.3e-8).
+// Vector instructions per wavefront 1435 -> 1067 (k1) and 1809 -> 1143 (k2).
+// Mhat^dag Mhat with 4, 8 sources on 16^4: 48 -> 40, 72 -> 64 us; 24^3x48: 297 ->
+// 267, 534 -> 517; 32^3x64: 875 -> 885, 1612 -> 1580 (4.8 TB/s in k1, 5.5 in k2).
+
+// entry of the link's row: M = (re, im); `re` = the operand of the real part
+// of M v, (re, -im), `im` = that of the imaginary part, (im, re)
+struct MfmaEntry {
+  unsigned int re, im;
+};
+template <bool ADJ>
+__device__ __forceinline__ MfmaEntry mfma_entry(unsigned int w) {
+  const unsigned int n = w ^ 0x80000000u;  // (re, -im)
+  if constexpr (ADJ) return {w, (n >> 16) | (n << 16)};
+  return {n, (w >> 16) | (w << 16)};
+}
+__device__ __forceinline__ unsigned int neg_h2(unsigned int w) { return w ^ 0x80008000u; }
+// the operands of f M, f = SG or (I) SG i
+template <bool I, int SG>
+__device__ __forceinline__ MfmaEntry mfma_phase(MfmaEntry e) {
+  if constexpr (!I) return SG > 0 ? e : MfmaEntry{neg_h2(e.re), neg_h2(e.im)};
+  return SG > 0 ? MfmaEntry{neg_h2(e.im), e.re} : MfmaEntry{e.im, neg_h2(e.re)};
+}
+typedef float f4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4_t mfma_step(unsigned int a0, unsigned int a1, unsigned int b0, unsigned int b1, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_4x4x4f16(as_h4(make_uint2(a0, a1)), as_h4(make_uint2(b0, b1)), c, 0, 0, 0);
+}
+// out = M times the upper two spins of (1 + S gamma_mu) psi (gamma_5 psi if
+// G5IN), psi's 12 components as stored in q, M's row (ADJ: of the adjoint) in u.
+template <int MU, int S, bool G5IN, bool ADJ>
+__device__ __forceinline__ void mfma_hop(const unsigned int q[12], const unsigned int u[3], Half<float>& out) {
+  constexpr bool I = MU == 0 || MU == 2;
+  constexpr int P = (S < 0 ? 1 : -1) * (G5IN ? -1 : 1);  // as in project()
+  constexpr int SG0 = MU == 3 ? -P : P, SG1 = MU == 0 ? P : -P;
+  constexpr int d0 = MU < 2 ? 9 : 6, d1 = MU < 2 ? 6 : 9;  // first component of the lower spin
+  MfmaEntry e[3], f0[3], f1[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    e[k] = mfma_entry<ADJ>(u[k]);
+    f0[k] = mfma_phase<I, SG0>(e[k]);
+    f1[k] = mfma_phase<I, SG1>(e[k]);
+  }
+  const f4_t z = {0.f, 0.f, 0.f, 0.f};
+  f4_t r0 = mfma_step(e[0].re, e[1].re, q[0], q[1], z);
+  f4_t i0 = mfma_step(e[0].im, e[1].im, q[0], q[1], z);
+  f4_t r1 = mfma_step(e[0].re, e[1].re, q[3], q[4], z);
+  f4_t i1 = mfma_step(e[0].im, e[1].im, q[3], q[4], z);
+  r0 = mfma_step(f0[0].re, f0[1].re, q[d0], q[d0 + 1], r0);
+  i0 = mfma_step(f0[0].im, f0[1].im, q[d0], q[d0 + 1], i0);
+  r1 = mfma_step(f1[0].re, f1[1].re, q[d1], q[d1 + 1], r1);
+  i1 = mfma_step(f1[0].im, f1[1].im, q[d1], q[d1 + 1], i1);
+  r0 = mfma_step(e[2].re, f0[2].re, q[2], q[d0 + 2], r0);
+  i0 = mfma_step(e[2].im, f0[2].im, q[2], q[d0 + 2], i0);
+  r1 = mfma_step(e[2].re, f1[2].re, q[5], q[d1 + 2], r1);
+  i1 = mfma_step(e[2].im, f1[2].im, q[5], q[d1 + 2], i1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    out.h[0][k] = {r0[k], i0[k]};
+    out.h[1][k] = {r1[k], i1[k]};
+  }
+}
+__device__ __forceinline__ void load_codes(const SpH& f, int e, unsigned int q[12]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint4 w = *elem(f.p, (size_t)k * 64, sph_at(e));
+    q[4 * k] = w.x;
+    q[4 * k + 1] = w.y;
+    q[4 * k + 2] = w.z;
+    q[4 * k + 3] = w.w;
+  }
+}
+// 12 i as a 32-bit offset: left to itself the compiler multiplies in 64 bits
+__device__ __forceinline__ unsigned times12(int i) {
+  unsigned o = (unsigned)i * 3u;
+  asm("" : "+v"(o));
+  return o << 2;
+}
+// hop_dir for these kernels; row: the lane's row (0, 1, 2, 2), row_at = row * stride
+template <int MU, bool G5IN, class A>
+__device__ __forceinline__ void hop_dir_mfma(const A& a, int i, int r, int row, int row_at, const int x[4], Spinor<float>& acc,
+                                             float cu, float cl) {
+  const Geom& g = a.g;
+  int y[4] = {x[0], x[1], x[2], x[3]};
+  y[MU] = (x[MU] + 1 == g.X[MU]) ? 0 : x[MU] + 1;
+  const int nf = lex(y, g) >> 1;
+  y[MU] = (x[MU] == 0 ? g.X[MU] : x[MU]) - 1;
+  const int nb = lex(y, g) >> 1;
+  const int ef = rhs_element<true>(nf, r, a.rhs), eb = rhs_element<true>(nb, r, a.rhs);
+  unsigned int qf[12], qb[12], ub[3];
+  load_codes(a.in, ef, qf);
+  const size_t df = (size_t)((MU * 2 + a.par_out) * 3) * a.U.stride;
+  const LinkRow uf = *(const LinkRow*)((const char*)(a.U.p + df) + times12(row_at + i));
+  load_codes(a.in, eb, qb);
+  const unsigned bo = times12(nb);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const size_t db = (size_t)((MU * 2 + 1 - a.par_out) * 3 + k) * a.U.stride;
+    ub[k] = *(const unsigned int*)((const char*)(a.U.p + db) + (bo + 4u * row));
+  }
+  float sf = scale_of(a.in, ef), sb = scale_of(a.in, eb);
+  if constexpr (MU == 3) {
+    sf = (g.tb < 0 && x[3] == g.X[3] - 1) ? -sf : sf;
+    sb = (g.tb < 0 && x[3] == 0) ? -sb : sb;
+  }
+  Half<float> uh;
+  mfma_hop<MU, -1, G5IN, false>(qf, uf.w, uh);
+  accumulate<MU, -1>(acc, uh, sf * cu, sf * cl);
+  mfma_hop<MU, +1, G5IN, true>(qb, ub, uh);
+  accumulate<MU, +1>(acc, uh, sb * cu, sb * cl);
+}
+
 // The site term's clover: general Hermitian blocks, or the compact form of
 // a clover term built from links.
 template <bool FUSED_CL, typename R, class CL>
@@ -165,26 +294,32 @@ __device__ __forceinline__ void site_clover(const CL& c, int i, Spinor<R>& s) {
     apply_clover<FUSED_CL>(c, i, s);
 }
 
-// MULTI: one work-item per (site, right-hand side) with the right-hand side
-// fastest, so the 1 << lg work-items of a site share its link and clover
-// loads; halted right-hand sides keep computing with alpha = 0 (the grid
-// cannot return early for some of them).
+// Several sources: one work-item per (site, right-hand side) with the
+// right-hand side fastest, so the work-items of a site share its link and
+// clover loads; halted right-hand sides keep computing with alpha = 0 (the
+// grid cannot return early for some of them).  As many as asked for: padding
+// to a power of two cost up to 16 / 9 of the work (9 sources on 16^4: 34.0 ms
+// a solve in FP64, 16.0 mixed; now 21.6 and 10.9).
 // Wavefronts per SIMD the register allocation must leave room for: FP32
-// k1 4 (121 registers), k2 5 (96) except with an FP32 clover (which would
-// spill there) and the single-source k2 with the compact clover (5 spills
-// 8 bytes per work-item; at 4, 103 registers and 2.6 % faster); FP64
-// kernels take what they need (2).
-template <typename R, int SITE, class A, bool MULTI>
+// k1 4 (121 registers); single-source k2 5 (96) except with an FP32 clover
+// (which would spill there) and with the compact clover (5 spills 8 bytes per
+// work-item; at 4, 103 registers and 2.6 % faster); multi-source k2 4, on the
+// matrix cores 3 (144; at 4 they spill and take 1.5 times as long, and k1, 106,
+// gains 2 % from 3); FP64 kernels take what they need (2).
+template <typename R, int SITE, class A, int SOURCES>
 constexpr int stencil_waves() {
+  constexpr bool MULTI = SOURCES != ONE_SOURCE;
   if (sizeof(R) == 8) return 1;
+  if (SOURCES == MULTI_MFMA) return 3;
   if (SITE == 2 && !MULTI && std::is_same<decltype(A::cpre), CloverHC>::value) return 4;
-  if (SITE == 2 && !std::is_same<decltype(A::cpre), CloverF32>::value) return 5;
+  if (SITE == 2 && !MULTI && !std::is_same<decltype(A::cpre), CloverF32>::value) return 5;
   return 4;
 }
 
-template <typename R, int SITE, bool POST, bool G5IN, bool MULTI, class A>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(stencil_waves<R, SITE, A, MULTI>())))
+template <typename R, int SITE, bool POST, bool G5IN, int SOURCES, class A>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(stencil_waves<R, SITE, A, SOURCES>())))
 dslash_kernel(A a) {
+  constexpr bool MULTI = SOURCES != ONE_SOURCE, POW2 = SOURCES != MULTI_ANY;
   // A launch that finishes alpha itself (fin_nr > 0, the dagger k1) may set
   // halt while it runs, so it does not read halt at all: it reads no alpha,
   // and the k2 that consumes its output returns early once halt is set.
@@ -195,18 +330,19 @@ dslash_kernel(A a) {
     return;
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   const int w = blk * blockDim.x + threadIdx.x;  // work position
-  const int r = MULTI ? (w & ((1 << a.lg) - 1)) : 0;
+  int r = 0, j = w;
+  if constexpr (MULTI) j = rhs_split<POW2>(w, a.rhs, r);
   double nrm = 0.0;
-  if ((MULTI ? (w >> a.lg) : w) < a.g.Vh) {
+  if (j < a.g.Vh) {
     int x[4];
     int i;  // checkerboard site
     if constexpr (MULTI) {
-      i = multi_site(a, w >> a.lg, x);
+      i = multi_site(a, j, x);
     } else {
       i = w;
       cb_coords(i, a.par_out, a.g, x);
     }
-    const int e = MULTI ? ((i << a.lg) | r) : i;  // spinor element
+    const int e = MULTI ? rhs_element<POW2>(i, r, a.rhs) : i;  // spinor element
     constexpr bool scaled = SpinorScale<decltype(a.in)>::scaled;
     // hop scale, with gamma5 on the output folded into the lower spins
     const R c = R(a.c), cl = a.g5out ? R(-a.c) : R(a.c);
@@ -232,10 +368,21 @@ dslash_kernel(A a) {
     }
     const R hu = HOP_IN_ACC ? c : R(1), hl = HOP_IN_ACC ? cl : R(1);
     constexpr bool SCALED_ACC = scaled || HOP_IN_ACC;
-    hop_dir<0, G5IN, MULTI, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
-    hop_dir<1, G5IN, MULTI, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
-    hop_dir<2, G5IN, MULTI, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
-    hop_dir<3, G5IN, MULTI, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
+    if constexpr (SOURCES == MULTI_MFMA) {
+      const int row = min((int)threadIdx.x & 3, 2), row_at = row * a.U.stride;
+      hop_dir_mfma<0, G5IN>(a, i, r, row, row_at, x, acc, hu, hl);
+      __builtin_amdgcn_sched_barrier(0);
+      hop_dir_mfma<1, G5IN>(a, i, r, row, row_at, x, acc, hu, hl);
+      __builtin_amdgcn_sched_barrier(0);
+      hop_dir_mfma<2, G5IN>(a, i, r, row, row_at, x, acc, hu, hl);
+      __builtin_amdgcn_sched_barrier(0);
+      hop_dir_mfma<3, G5IN>(a, i, r, row, row_at, x, acc, hu, hl);
+    } else {
+      hop_dir<0, G5IN, SOURCES, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
+      hop_dir<1, G5IN, SOURCES, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
+      hop_dir<2, G5IN, SOURCES, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
+      hop_dir<3, G5IN, SOURCES, FUSED, SCALED_ACC>(a, i, r, x, acc, hu, hl);
+    }
     if constexpr (!HOP_IN_CLOVER && !HOP_IN_ACC) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -281,7 +428,7 @@ dslash_kernel(A a) {
   }
   if (a.epi >= 1) {
     if constexpr (MULTI)
-      block_sum_store_seg(nrm, a.partial, blk, gridDim.x, a.lg);
+      block_sum_store_seg<POW2>(nrm, a.partial, blk, gridDim.x, a.rhs);
     else
       block_sum_store(nrm, a.partial, blk);
   }
@@ -687,8 +834,11 @@ LinkH12 lk_of<LinkH12>(const void* p, int stride) {
 }
 template <>
 LinkH18 lk_of<LinkH18>(const void* p, int stride) {
-  const uint4* c = (const uint4*)p;
-  return LinkH18{c, (const unsigned int*)(c + (size_t)16 * stride), stride};
+  return LinkH18{(const LinkRow*)p, stride};
+}
+template <>
+LinkH18Stream lk_of<LinkH18Stream>(const void* p, int stride) {
+  return LinkH18Stream{lk_of<LinkH18>(p, stride)};
 }
 
 // one work-item per site: up to this many sites the grid has less than one
@@ -699,14 +849,14 @@ bool stencil_reads_user(const Geom& g, int small_grid, int block) {
   return g.Vh <= kSmallVh && small_grid == 2 && block == 64;
 }
 static bool small_direct(const Geom& g, const DslashOp& op, int block) {
-  return op.lg == 0 && stencil_reads_user(g, op.small_grid, block);
+  return op.nr == 1 && stencil_reads_user(g, op.small_grid, block);
 }
 
 template <typename R, class SIn, class SSite, class SOut, class LK, class CPre, class CPost, int SITE, bool POST,
           bool G5IN>
 static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
   DArgs<SIn, SSite, SOut, LK, CPre, CPost> a;
-  const int ss = g.stride << op.lg;  // spinor stride: all right-hand sides
+  const int ss = g.stride * op.nr;  // spinor stride: all right-hand sides
   a.g = g;
   a.par_out = op.par_out;
   a.in = sp_of<SIn>(op.in, ss);
@@ -724,7 +874,7 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
   a.g5out = op.g5out;
   a.st = op.st;
   a.partial = op.partial;
-  a.lg = op.lg;
+  a.rhs = rhs_div(op.nr);
   a.tile_lg = 0;
   while (a.tile_lg < 2 && g.X[2] % (2 << a.tile_lg) == 0) ++a.tile_lg;
   a.plane = g.Xh * g.X[1];
@@ -735,15 +885,15 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
   a.fin_partial = op.fin_partial;
   a.fin_n = op.fin_n;
   a.fin_nr = op.fin_nr;
-  const int nb = blocks_for(g.Vh << op.lg, block);
+  const int nb = blocks_for(g.Vh * op.nr, block);
   // the four-wavefront kernel takes the caller's arrays everywhere, the one
   // with a work-item per site for the result (and the others never)
   constexpr bool user_in = std::is_same<SIn, SpUser>::value || std::is_same<SSite, SpUser>::value;
   constexpr bool user_out = std::is_same<SOut, SpUser>::value;
   if constexpr (user_out && !user_in) {
     if (!small_direct(g, op, block)) {
-      if (op.lg > 0 || op.epi != 0) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, false, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+      if (op.nr > 1 || op.epi != 0) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, ONE_SOURCE, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
       return hipGetLastError();
     }
   }
@@ -753,18 +903,38 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
     hipLaunchKernelGGL((dslash_quad_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(both ? 2 * nb : nb), dim3(256), 0, s, a);
     return hipGetLastError();
   } else {
-  constexpr bool multi_only = std::is_same<LK, LinkH18>::value;  // 18-entry links serve the multi-source kernels
-  if (op.lg > 0)
-    hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, true, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
-  else if constexpr (multi_only)
-    return hipErrorInvalidValue;
-  else if (g.Vh <= kSmallVh && op.small_grid == 1 && block == 64)
+  // several sources: the 18-entry binary16 links serve nothing else, the
+  // 12-entry ones never; FP64 uses the same links
+  constexpr bool h18 = std::is_base_of<LinkH18, LK>::value, h12 = std::is_same<LK, LinkH12>::value;
+  const bool pow2 = (op.nr & (op.nr - 1)) == 0;
+  if constexpr (!h12) {
+    if (op.nr > 1) {
+      if constexpr (std::is_same<LK, LinkH18>::value) {
+        if (pow2 && op.nr >= 4) {
+          hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, MULTI_MFMA, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+          return hipGetLastError();
+        }
+      }
+      if (pow2)
+        hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, MULTI_POW2, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+      else if constexpr (!std::is_same<LK, LinkH18Stream>::value)
+        hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, MULTI_ANY, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+      else
+        return hipErrorInvalidValue;
+      return hipGetLastError();
+    }
+  }
+  if constexpr (h18) return hipErrorInvalidValue;
+  else {
+  if (h12 && op.nr > 1) return hipErrorInvalidValue;
+  if (g.Vh <= kSmallVh && op.small_grid == 1 && block == 64)
     hipLaunchKernelGGL((dslash_pair_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(nb), dim3(128), 0, s, a);
   else if (small_direct(g, op, block))
     hipLaunchKernelGGL((dslash_quad_kernel<R, SITE, POST, G5IN, decltype(a)>), dim3(nb), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, false, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
+    hipLaunchKernelGGL((dslash_kernel<R, SITE, POST, G5IN, ONE_SOURCE, decltype(a)>), dim3(nb), dim3(block), 0, s, a);
   return hipGetLastError();
+  }
   }
 }
 
@@ -838,6 +1008,22 @@ static hipError_t run_mixed(const Geom& g, const DslashOp& op, int block, hipStr
   return hipErrorInvalidValue;
 }
 
+template <class LK>
+static hipError_t run_multi(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
+  const int ck = op.post ? op.cpost.kind : op.cpre.kind;
+  if (ck == CL_F32) return run_mixed<CloverF32, LK>(g, op, block, s);
+  if (ck == CL_H) return run_mixed<CloverH, LK>(g, op, block, s);
+  if (ck == CL_HC && op.site_mode == 2 && !op.post)
+    return run<float, SpH, SpH, SpH, LK, CloverHC, CloverNone, 2, false>(g, op, block, s);
+  return hipErrorInvalidValue;
+}
+// The links (288 bytes per site of a parity) no longer fit the last-level
+// cache of 256 MB: with two sources, which reuse them least, streaming loads
+// then leave it to the spinors (Mhat^dag Mhat at 32^3x64, 302 MB: 553 us against
+// 582; at 24^3x48, 95 MB, 195 against 171 and at 16^4 38.7 against 33.2).
+// With three sources both take 777 us at 32^3x64.
+constexpr int kStreamVh = (256 << 20) / 288;
+
 hipError_t launch_dslash(const Geom& g, const DslashOp& op, int block, hipStream_t s) {
   if (op.in.kind == SP_F64 || is_user(op.in)) {
     if (op.link_kind == LK_F64_12) return run_f64<6>(g, op, block, s);
@@ -851,29 +1037,26 @@ hipError_t launch_dslash(const Geom& g, const DslashOp& op, int block, hipStream
     if (ck == CL_HC && op.site_mode == 2 && !op.post)
       return run<float, SpH, SpH, SpH, LinkH12, CloverHC, CloverNone, 2, false>(g, op, block, s);
   }
-  if (op.in.kind == SP_H && op.link_kind == LK_H18 && op.lg > 0) {
-    const int ck = op.post ? op.cpost.kind : op.cpre.kind;
-    if (ck == CL_F32) return run_mixed<CloverF32, LinkH18>(g, op, block, s);
-    if (ck == CL_H) return run_mixed<CloverH, LinkH18>(g, op, block, s);
-    if (ck == CL_HC && op.site_mode == 2 && !op.post)
-      return run<float, SpH, SpH, SpH, LinkH18, CloverHC, CloverNone, 2, false>(g, op, block, s);
-  }
+  if (op.in.kind == SP_H && op.link_kind == LK_H18 && op.nr > 1)
+    return op.nr == 2 && g.Vh >= kStreamVh ? run_multi<LinkH18Stream>(g, op, block, s)
+                                           : run_multi<LinkH18>(g, op, block, s);
   return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------------ clover only
-// element e = (cb << lg) | r
-__global__ void __launch_bounds__(256) clover_apply_kernel(Geom g, int lg, SpF64 in, SpF64 out, CloverF64 c) {
+__global__ void __launch_bounds__(256) clover_apply_kernel(Geom g, RhsDiv d, SpF64 in, SpF64 out, CloverF64 c) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (g.Vh << lg)) return;
+  int r;
+  const int i = rhs_split(e, d, r);
+  if (i >= g.Vh) return;
   Spinor<double> v;
   load(in, e, v);
-  apply_clover(c, e >> lg, v);
+  apply_clover(c, i, v);
   store(out, e, v);
 }
 
-hipError_t launch_clover_apply(const Geom& g, int lg, SpF64 in, SpF64 out, const double2* clov, hipStream_t s) {
-  hipLaunchKernelGGL(clover_apply_kernel, dim3(blocks_for(g.Vh << lg, 256)), dim3(256), 0, s, g, lg, in, out,
+hipError_t launch_clover_apply(const Geom& g, int nr, SpF64 in, SpF64 out, const double2* clov, hipStream_t s) {
+  hipLaunchKernelGGL(clover_apply_kernel, dim3(blocks_for(g.Vh * nr, 256)), dim3(256), 0, s, g, rhs_div(nr), in, out,
                      CloverF64{clov, g.stride});
   return hipGetLastError();
 }

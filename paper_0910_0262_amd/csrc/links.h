@@ -34,19 +34,13 @@ __device__ __forceinline__ void store_copies(const LinkCopies& c, int stride, in
   }
   if (c.uh18 != nullptr) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      h8_t h;
+    for (int k = 0; k < 3; ++k) {
+      unsigned int w[3];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        h[2 * j] = (_Float16)(float)r[4 * k + j].x;
-        h[2 * j + 1] = (_Float16)(float)r[4 * k + j].y;
-      }
-      *elem(c.uh18, (size_t)(q * 2 + k) * stride, cb) = from_h8(h);
+      for (int j = 0; j < 3; ++j)
+        w[j] = from_h2(h2_t{(_Float16)(float)r[3 * k + j].x, (_Float16)(float)r[3 * k + j].y});
+      *elem(c.uh18, (size_t)(q * 3 + k) * stride, cb) = LinkRow{w[0], w[1], w[2]};
     }
-    h2_t h;
-    h[0] = (_Float16)(float)r[8].x;
-    h[1] = (_Float16)(float)r[8].y;
-    *elem((unsigned int*)(c.uh18 + (size_t)16 * stride), (size_t)q * stride, cb) = from_h2(h);
   }
 }
 

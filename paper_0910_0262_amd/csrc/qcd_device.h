@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace qcd {
 
 // ------------------------------------------------------------------ complex
@@ -244,6 +246,35 @@ __device__ __forceinline__ int fdivmod(int n, int d, double inv, int& r) {
     r -= d;
   }
   return q;
+}
+
+// Element e = cb * n + r of n interleaved right-hand sides.  mul = ceil(2^32 /
+// n), and the upper half of e * mul is the quotient for e < 2^28 (the host
+// keeps 48 e below 2^32 where n > 1).  POW2: n = 1 << lg, by shifts: the four
+// quarter-rate multiplications between a stencil's work-item and its first
+// load cost 0.4 us a launch on small lattices (3 % of a solve at 8^3x16).
+struct RhsDiv {
+  int n, lg;
+  unsigned mul;
+};
+inline RhsDiv rhs_div(int n) {
+  RhsDiv d{n, 0, n > 1 ? 0xffffffffu / (unsigned)n + 1u : 0u};
+  while ((2 << d.lg) <= n) ++d.lg;
+  return d;
+}
+template <bool POW2 = false>
+__device__ __forceinline__ int rhs_split(int e, RhsDiv d, int& r) {
+  if constexpr (POW2) {
+    r = e & ((1 << d.lg) - 1);
+    return e >> d.lg;
+  }
+  const int q = d.n == 1 ? e : (int)__umulhi((unsigned)e, d.mul);
+  r = e - q * d.n;
+  return q;
+}
+template <bool POW2>
+__device__ __forceinline__ int rhs_element(int cb, int r, RhsDiv d) {
+  return POW2 ? (cb << d.lg) | r : cb * d.n + r;
 }
 
 __device__ __forceinline__ void cb_coords(int cb, int par, const Geom& g, int x[4]) {
@@ -568,15 +599,20 @@ struct LinkH12 {
 };
 // All nine entries as 18 x binary16 (36 B / link), for the multi-source
 // kernels, whose vector-instruction issue the row rebuild would cost more
-// than the 12 extra bytes (shared by all right-hand sides of a site): chunks
-// 0 and 1 (8 halves each) at p[((mu * 2 + par) * 2 + k) * stride + cb],
-// chunk 2 (the last entry) at q[(mu * 2 + par) * stride + cb]; q follows the
-// 16 * stride chunks of p in the same allocation.
+// than the 12 extra bytes (shared by all right-hand sides of a site): row k
+// at p[((mu * 2 + par) * 3 + k) * stride + cb], so that a work-item gets a row
+// in one load and a column in three from one address.
+struct LinkRow {
+  unsigned int w[3];
+};
 struct LinkH18 {
-  const uint4* p;
-  const unsigned int* q;
+  const LinkRow* p;
   int stride;
 };
+struct LinkH18Stream : LinkH18 {};  // read with streaming loads
+__device__ __forceinline__ LinkRow ld_stream(const LinkRow* p) {
+  return {{ld_stream(&p->w[0]), ld_stream(&p->w[1]), ld_stream(&p->w[2])}};
+}
 
 template <typename R>
 __device__ __forceinline__ void reconstruct_row2(Mat<R>& u) {
@@ -595,18 +631,19 @@ __device__ __forceinline__ void load_link(const LinkF64<NC>& f, int mu, int par,
   }
   if (NC == 6) reconstruct_row2(u);
 }
-template <typename R>
-__device__ __forceinline__ void load_link(const LinkH18& f, int mu, int par, int i, Mat<R>& u) {
+template <typename R, class LK, typename std::enable_if<std::is_base_of<LinkH18, LK>::value, int>::type = 0>
+__device__ __forceinline__ void load_link(const LK& f, int mu, int par, int i, Mat<R>& u) {
   const int d = mu * 2 + par;
-  const h8_t a = as_h8(ld_stream(elem(f.p, (size_t)(d * 2) * f.stride, i)));
-  const h8_t b = as_h8(ld_stream(elem(f.p, (size_t)(d * 2 + 1) * f.stride, i)));
-  const h2_t c = as_h2(ld_stream(elem(f.q, (size_t)d * f.stride, i)));
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    u.m[k / 3][k % 3] = {R(float(a[2 * k])), R(float(a[2 * k + 1]))};
-    u.m[(k + 4) / 3][(k + 4) % 3] = {R(float(b[2 * k])), R(float(b[2 * k + 1]))};
+  for (int k = 0; k < 3; ++k) {
+    const LinkRow* const at = elem(f.p, (size_t)(d * 3 + k) * f.stride, i);
+    const LinkRow row = std::is_same<LK, LinkH18Stream>::value ? ld_stream(at) : *at;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const h2_t h = as_h2(row.w[j]);
+      u.m[k][j] = {R(float(h[0])), R(float(h[1]))};
+    }
   }
-  u.m[2][2] = {R(float(c[0])), R(float(c[1]))};
 }
 template <typename R>
 __device__ __forceinline__ void load_link(const LinkH12& f, int mu, int par, int i, Mat<R>& u) {
@@ -1040,16 +1077,29 @@ __device__ __forceinline__ void block_sum_store(double v, double* partial, int s
   }
 }
 
-// Segmented version for 1 << lg (<= 16) interleaved right-hand sides: thread
-// t contributes to right-hand side t & ((1 << lg) - 1); the workgroup's sum
-// for right-hand side r goes to partial[r * nblk + slot].  lg = 0 gives the
-// same sums, in the same order, as block_sum_store.
-__device__ __forceinline__ void block_sum_store_seg(double v, double* partial, int slot, int nblk, int lg) {
-  const int nr = 1 << lg;
-  for (int off = 32; off >= nr; off >>= 1) v += __shfl_down(v, off, 64);
-  __shared__ double red[16][16];
+// Segmented version for d.n (<= 16) interleaved right-hand sides: work-item w
+// (over the grid, the workgroup at place `slot`) contributes to right-hand
+// side w mod d.n; the workgroup's sum for right-hand side r goes to
+// partial[r * nblk + slot].  One right-hand side gives the same sums, in the
+// same order, as block_sum_store.
+template <bool POW2 = false>
+__device__ __forceinline__ void block_sum_store_seg(double v, double* partial, int slot, int nblk, RhsDiv d) {
+  const int nr = d.n;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane < nr) red[w][lane] = v;
+  int r = lane;
+  if constexpr (POW2) {
+    for (int off = 32; off >= nr; off >>= 1) v += __shfl_down(v, off, 64);
+  } else {
+    int off = nr;
+    while (2 * off < 64) off *= 2;
+    for (; off >= nr; off >>= 1) {  // nr times a power of two: lanes of the same right-hand side
+      const double t = __shfl_down(v, off, 64);
+      if (lane + off < 64) v += t;
+    }
+    (void)rhs_split((int)(slot * blockDim.x) + (w << 6) + lane, d, r);
+  }
+  __shared__ double red[16][16];
+  if (lane < nr) red[w][r] = v;
   __syncthreads();
   if ((int)threadIdx.x < nr) {
     double s = 0.0;

@@ -142,10 +142,10 @@ struct DslashOp {
   const CgState* st;
   double* partial;
   // Several right-hand sides interleaved site by site: spinor element v =
-  // (cb << lg) | r holds right-hand side r of checkerboard site cb; links and
-  // clover are indexed by cb and shared.  st then points at 1 << lg states
+  // cb * nr + r holds right-hand side r of checkerboard site cb; links and
+  // clover are indexed by cb and shared.  st then points at nr states
   // and the partial sums of right-hand side r start at partial[r * blocks].
-  int lg;
+  int nr = 1;
   // single-source kernel on small lattices: 0 one work-item per site, 1 two
   // wavefronts per 64 sites, 2 four
   int small_grid;
@@ -164,7 +164,7 @@ inline int blocks_for(int n, int block) { return (n + block - 1) / block; }
 // Whether the single-source stencils run the small-lattice form that takes the caller's arrays
 bool stencil_reads_user(const Geom& g, int small_grid, int block);
 hipError_t launch_dslash(const Geom& g, const DslashOp& op, int block, hipStream_t s);
-hipError_t launch_clover_apply(const Geom& g, int lg, SpF64 in, SpF64 out, const double2* clov, hipStream_t s);
+hipError_t launch_clover_apply(const Geom& g, int nr, SpF64 in, SpF64 out, const double2* clov, hipStream_t s);
 
 // ---- blas.hip
 hipError_t launch_pack_spinor_full(const Geom& g, const double2* user, SpF64 e, SpF64 o, hipStream_t s);
@@ -172,17 +172,17 @@ hipError_t launch_unpack_spinor_full(const Geom& g, SpF64 e, SpF64 o, double2* u
 hipError_t launch_pack_spinor_cb(const Geom& g, const double2* user, SpF64 f, hipStream_t s);
 hipError_t launch_unpack_spinor_cb(const Geom& g, SpF64 f, double2* user, hipStream_t s);
 // n right-hand sides, caller layout [n][V][4][3] complex128, into the
-// interleaved even / odd fields (rhs slots n .. (1 << lg) - 1 are zero)
-hipError_t launch_pack_spinor_multi(const Geom& g, int lg, int n, const double2* user, SpF64 e, SpF64 o,
+// interleaved even / odd fields
+hipError_t launch_pack_spinor_multi(const Geom& g, int n, const double2* user, SpF64 e, SpF64 o,
                                     hipStream_t s);
-hipError_t launch_unpack_spinor_multi(const Geom& g, int lg, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s);
+hipError_t launch_unpack_spinor_multi(const Geom& g, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s);
 // Copies of the links the stencils read, any of them null where it is not
 // wanted.  u12: FP64 rows 0, 1; uh: binary16 rows 0, 1; uh18: all nine binary16
 // entries (16 * stride uint4 chunks followed by 8 * stride 32-bit chunks).
 struct LinkCopies {
   double2* u12 = nullptr;
   uint2* uh = nullptr;
-  uint4* uh18 = nullptr;
+  LinkRow* uh18 = nullptr;
 };
 hipError_t launch_pack_gauge(const Geom& g, const double2* user, double2* u18, const LinkCopies& c, hipStream_t s);
 hipError_t launch_unpack_gauge(const Geom& g, const double2* u18, double2* user, hipStream_t s);
@@ -191,9 +191,9 @@ hipError_t launch_pack_clover(const Geom& g, const double2* user, double2* clov,
 hipError_t launch_unpack_clover(const Geom& g, const double2* clov, double2* user, int n_par, int par0,
                                 hipStream_t s);
 // Spinor BLAS: gv is the geometry with Vh and stride scaled by the number of
-// right-hand sides (1 << lg); per-rhs states and segmented partial sums.
-hipError_t launch_norm2(const Geom& gv, int lg, SpRef x, double* partial, int block, hipStream_t s);
-hipError_t launch_dot_re(const Geom& gv, int lg, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s);
+// right-hand sides (nr); per-rhs states and segmented partial sums.
+hipError_t launch_norm2(const Geom& gv, int nr, SpRef x, double* partial, int block, hipStream_t s);
+hipError_t launch_dot_re(const Geom& gv, int nr, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s);
 // Finalisation kernels: one workgroup per right-hand side (nr of them), each
 // summing its n partials and updating its own state.  With kFoldMin or more
 // partials per right-hand side they are first folded, by one workgroup per
@@ -213,14 +213,14 @@ hipError_t launch_fin_beta(CgState* st, const double* partial, int n, int nr, do
 hipError_t launch_fin_ru(CgState* st, const double* partial, int n, int nr, double* fold, int restart, int nclear,
                          Mail* mbox, int ring, hipStream_t s);
 // Iteration j of an n-iteration x cycle; p[0 .. n-1] are the cycle's direction buffers.
-hipError_t launch_xp_update_f64(const Geom& gv, int lg, const CgState* st, SpF64 x, const SpF64* p, int j, int n,
+hipError_t launch_xp_update_f64(const Geom& gv, int nr, const CgState* st, SpF64 x, const SpF64* p, int j, int n,
                                 SpF64 r, int block, hipStream_t s);
-hipError_t launch_xp_update_h(const Geom& gv, int lg, const CgState* st, SpF32 x, const SpH* p, int j, int n, SpH r,
+hipError_t launch_xp_update_h(const Geom& gv, int nr, const CgState* st, SpF32 x, const SpH* p, int j, int n, SpH r,
                               int block, hipStream_t s);
-hipError_t launch_p_restart_f64(const Geom& gv, int lg, const CgState* st, SpF64 p, SpF64 r, int block,
+hipError_t launch_p_restart_f64(const Geom& gv, int nr, const CgState* st, SpF64 p, SpF64 r, int block,
                                 hipStream_t s);
 // x_hi += x_lo + the first q directions p[0 .. q-1] of the unfinished cycle; x_lo = 0
-hipError_t launch_ru_accum(const Geom& gv, int lg, const CgState* st, SpF64 xhi, SpF32 xlo, const SpH* p, int q,
+hipError_t launch_ru_accum(const Geom& gv, int nr, const CgState* st, SpF64 xhi, SpF32 xlo, const SpH* p, int q,
                            int block, hipStream_t s);
 hipError_t launch_convert(const Geom& g, SpRef src, SpRef dst, int block, hipStream_t s);
 hipError_t launch_zero(const Geom& g, SpRef x, int block, hipStream_t s);
