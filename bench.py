@@ -46,13 +46,13 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_dslash_32x32x32x64.md")
 # k1 launches of the multi-source solves (mixed: the timed headline; FP64:
 # its reliable updates and the FP64 solve) and of the single-source ones
 TRAFFIC_KERNELS = {
-    "k2_mixed_multi": ("dslash_kernel<float, 2, false, false, true,", "LinkH18, qcd::CloverHC,"),
-    "k1_mixed_multi": ("dslash_kernel<float, 0, true, false, true,", "LinkH18", "CloverH>"),
-    "k1_mixed_single": ("dslash_kernel<float, 0, true, false, false,", "LinkH12", "CloverH>"),
-    "k2_fp64_multi": ("dslash_kernel<double, 2, false, false, true,", "qcd::CloverF64C, qcd::CloverNone>"),
-    "k1_fp64_multi": ("dslash_kernel<double, 0, true, false, true,", "qcd::CloverNone, qcd::CloverF64>"),
-    "k2_fp64_single": ("dslash_kernel<double, 2, false, false, false,", "qcd::CloverF64C, qcd::CloverNone>"),
-    "k1_fp64_single": ("dslash_kernel<double, 0, true, false, false,", "qcd::CloverNone, qcd::CloverF64>"),
+    "k2_mixed_multi": ("dslash_kernel<float, 2, false, false, 3,", "LinkH18, qcd::CloverHC,"),
+    "k1_mixed_multi": ("dslash_kernel<float, 0, true, false, 3,", "LinkH18", "CloverH>"),
+    "k1_mixed_single": ("dslash_kernel<float, 0, true, false, 0,", "LinkH12", "CloverH>"),
+    "k2_fp64_multi": ("dslash_kernel<double, 2, false, false, 1,", "qcd::CloverF64C, qcd::CloverNone>"),
+    "k1_fp64_multi": ("dslash_kernel<double, 0, true, false, 1,", "qcd::CloverNone, qcd::CloverF64>"),
+    "k2_fp64_single": ("dslash_kernel<double, 2, false, false, 0,", "qcd::CloverF64C, qcd::CloverNone>"),
+    "k1_fp64_single": ("dslash_kernel<double, 0, true, false, 0,", "qcd::CloverNone, qcd::CloverF64>"),
 }
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_0910_0262_amd", "csrc", f) for f in ("qcd_device.h", "qcd_internal.h", "dslash.hip")]
 
@@ -536,7 +536,7 @@ def main() -> int:
     head = mdagm_multi["mixed"] if NR > 1 else mdagm["mixed"]
     clover_name = "FP32" if mc == 32 else "binary16"
 
-    def alu_or_hbm(which: str):
+    def stencil_roofline(which: str):
         k = "k2" if which == "k2" else "k1"
         if NR > 1:
             nbytes = (k2_bytes_multi if k == "k2" else k1_bytes_multi)("mixed", NR, mc) * Vh
@@ -547,28 +547,28 @@ def main() -> int:
         tkey = f"{k}_mixed_{'multi' if NR > 1 else 'single'}"
         traffic = traffic_for(tkey, Vh) if (mc == 16 and (NR == 8 or NR == 1)) else None
         what = ("k2: A_ee p_e - kappa^2 H_eo t_o" if k == "k2" else "k1: t_o = A_oo^-1 H_oe p_e")
+        # the kernel's sources: one, a power of two, any number, a power of two from 4 on
+        sources = 0 if NR == 1 else 2 if NR & (NR - 1) else 3 if NR >= 4 else 1
         kname = (f"dslash_kernel<float, {2 if k == 'k2' else 0}, {'false' if k == 'k2' else 'true'}, false, "
-                 f"{'true' if NR > 1 else 'false'}, ...> (mixed {what} for {NR} interleaved sources, binary16 "
+                 f"{sources}, ...> (mixed {what} for {NR} interleaved sources, binary16 "
                  f"spinors/links, {clover_name} clover)")
-        if NR > 1:
-            achieved = flops / secs / 1e12
-            return {"bound": "alu", "achieved": achieved, "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": achieved / FP32_VALU_PEAK_TFLOPS, "traffic": traffic, "kernel": kname,
-                    "flops_per_launch": flops, "bytes_per_launch": nbytes,
-                    "hbm_GB_s": nbytes / secs / 1e9, "hbm_frac": nbytes / secs / 1e9 / HBM_PEAK_GBS}
         achieved = nbytes / secs / 1e9
-        return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kname, "bytes_per_launch": nbytes}
+        out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+               "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kname, "bytes_per_launch": nbytes}
+        if NR > 1:
+            tflops = flops / secs / 1e12
+            out.update({"flops_per_launch": flops, "tflops": tflops, "valu_frac": tflops / FP32_VALU_PEAK_TFLOPS})
+        return out
 
-    roofline = alu_or_hbm("k2")
-    roofline_k1 = alu_or_hbm("k1")
+    roofline = stencil_roofline("k2")
+    roofline_k1 = stencil_roofline("k1")
     # the single-source k1, HBM-bound, for reference
     s_k1 = mdagm["mixed"]["k1_ms"] * 1e-3
     s_bytes = k1_bytes_per_site("mixed", mixed_clover=mc) * Vh
     roofline_single = {"bound": "hbm", "achieved": s_bytes / s_k1 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                        "frac": s_bytes / s_k1 / 1e9 / HBM_PEAK_GBS,
                        "traffic": traffic_for("k1_mixed_single", Vh) if mc == 16 else None,
-                       "kernel": "dslash_kernel<float, 0, true, false, false, ...CloverH> (mixed k1, one source)",
+                       "kernel": "dslash_kernel<float, 0, true, false, 0, ...CloverH> (mixed k1, one source)",
                        "bytes_per_launch": s_bytes}
 
     out = {
