@@ -86,9 +86,9 @@ typedef enum {
                                per-block FP32 scale (default), 32 = FP32                */
   QCD_OPT_BLOCK = 2,        /* threads per workgroup of the stencil and reduction
                                kernels (64, 128, 192 or 256); 0 (default) = 64 for
-                               single-source work, 256 for multi-source solves of 2 or
-                               more right-hand sides.  The CG x/p update always runs
-                               in 64-thread workgroups.                                 */
+                               single-source work, for several right-hand sides 256, or
+                               fewer where that spreads a small launch more evenly.
+                               The CG x/p update always runs in 64-thread workgroups.   */
   QCD_OPT_GRAPH = 3,        /* 1: each CG iteration is replayed as a captured HIP graph;
                                0 (default): its kernels are launched one by one (graph
                                replay measured no faster on MI355X)                     */

@@ -77,6 +77,35 @@ struct Work {
   unsigned int post_ctr = 0;     // host mirror of CgState::post_seq (equal for all nr states)
 };
 
+// Workgroup of the multi-source kernels on n elements (sites times right-hand
+// sides).  256 gives a quarter of the partial sums, but while all wavefronts
+// are resident at once (up to 2048, eight to a CU) a launch takes as long as
+// the CU with the most of them: the workgroup that makes that number least,
+// the largest of equals.  Solves, us, with 256 | 128 | 64 (the rule's choice in
+// brackets): FP64 8^3x16, 2 sources 4042 | 3599 | [3396], 8 sources 4549 |
+// [4182] | 4197, 16 sources [5279] | 5528 | 5362; 12^3x24, 3 sources [6195] |
+// 6218 | 6249, 4 sources 8937 | [7732] | 7967; 16^4, 3 sources 9489 | [8365] |
+// 8571, 4 sources [10011] | 10037 | 10351; mixed 16^4, 3 sources 5559 | [5306] |
+// 5553.  A gain of less than a quarter is not worth smaller workgroups (12^3x16,
+// 8 sources, 8 against 7 wavefronts: mixed [4882] with 256, 5040 with 64; FP64
+// [8576] and 8430), and with more wavefronts 256 leads (16^4, 5 sources
+// [13388] | 13672 | 13607, 6 sources [14215] | 15634 | 14553).
+int multi_block(int n) {
+  constexpr int kCus = 256;
+  const int waves = blocks_for(n, 64);
+  if (waves > 8 * kCus) return 256;
+  const int most256 = 4 * blocks_for(blocks_for(n, 256), kCus);
+  int best = 256, least = most256;
+  for (int b = 128; b >= 64; b /= 2) {
+    const int most = (b / 64) * blocks_for(blocks_for(n, b), kCus);
+    if (most < least && 4 * most <= 3 * most256) {
+      best = b;
+      least = most;
+    }
+  }
+  return best;
+}
+
 struct qcd_ctx {
   int dims[4];
   Geom g;
@@ -142,10 +171,10 @@ struct qcd_ctx {
   LinkCopies all_copies() const { return copies(true, true, true); }
 
   // Workgroup size of the stencils and reductions, measured: 64 threads for
-  // single-source work; 256 for the multi-source set, where FP64 solves are
-  // about 1 % faster than at 64 and mixed ones equal (the x/p update keeps
-  // 64 threads, kXpBlock).
-  int block() const { return block_opt ? block_opt : (w->nr > 1 ? 256 : 64); }
+  // single-source work; multi_block() for several sources: on large lattices
+  // 256, where FP64 solves are about 1 % faster than at 64 and mixed ones equal
+  // (the x/p update keeps 64 threads, kXpBlock).
+  int block() const { return block_opt ? block_opt : (w->nr > 1 ? multi_block(w->gv.Vh) : 64); }
   SpF64 f64(int s) const { return SpF64{w->vec[s], w->gv.stride}; }
   SpRef ref64(int s) const { return SpRef{SP_F64, w->vec[s], nullptr}; }
   SpRef refh(int s) const { return SpRef{SP_H, w->hv[s], w->hs[s]}; }
