@@ -638,13 +638,19 @@ int launch_iter(qcd_ctx* c, bool mixed, int j) {
   return QCD_OK;
 }
 
-void drop_graphs(qcd_ctx* c) {
+// A solve that failed (QCD_ENAN) leaves iterations on the stream, so a graph
+// goes only once the stream has run what was launched.
+int drop_graphs(qcd_ctx* c) {
+  bool waited = false;
   for (auto& row : c->iter_graph)
     for (auto& gx : row)
       if (gx) {
+        if (!waited) HIPCHK(hipStreamSynchronize(c->stream));
+        waited = true;
         (void)hipGraphExecDestroy(gx);
         gx = nullptr;
       }
+  return QCD_OK;
 }
 
 // Capture one iteration on the private stream into an executable graph.
@@ -973,15 +979,14 @@ int qcd_set_params(qcd_ctx* c, double kappa, double csw, int t_boundary) {
   c->tb = t_boundary;
   c->g.tb = t_boundary;
   c->clover_ready = false;
-  drop_graphs(c);
-  return QCD_OK;
+  return drop_graphs(c);
 }
 
 static int clover_copy32(qcd_ctx* c);
 
 int qcd_set_option(qcd_ctx* c, int option, int value) {
   QCHK(check_ctx(c));
-  drop_graphs(c);
+  QCHK(drop_graphs(c));
   switch (option) {
     case QCD_OPT_LINK_RECON:
       if (value != 12 && value != 18) return fail(QCD_EINVAL, "link reconstruction must be 12 or 18");
