@@ -75,6 +75,8 @@ struct Work {
   Mail* mbox_host = nullptr;     // host-mapped rings of posted states: [nr][kRing]
   Mail* mbox_dev = nullptr;      // device address of mbox_host
   unsigned int post_ctr = 0;     // host mirror of CgState::post_seq (equal for all nr states)
+  // one CG iteration on these buffers: [FP64, mixed][position in the x cycle]
+  hipGraphExec_t iter_graph[2][4] = {};
 };
 
 // Workgroup of the multi-source kernels on n elements (sites times right-hand
@@ -148,7 +150,6 @@ struct qcd_ctx {
   Work* w = &w1;    // the set the solver drivers use
   int wm_alloc = 0;  // right-hand sides wm was allocated for
   hipStream_t cap = nullptr;    // private stream used only to capture graphs
-  hipGraphExec_t iter_graph[2][4] = {};  // one CG iteration: [FP64, mixed][position in the x cycle]
   int* status = nullptr;       // device address of status_host
   int* status_host = nullptr;  // host-mapped
   double2* xi = nullptr;       // clover-force Xi: [par][6][kXiChunks][stride]
@@ -199,7 +200,18 @@ int dalloc(T** p, size_t bytes) {
   return QCD_OK;
 }
 
+// The stream has run what was launched on the work set.
+void drop_graphs(Work& w) {
+  for (auto& row : w.iter_graph)
+    for (auto& gx : row)
+      if (gx) {
+        (void)hipGraphExecDestroy(gx);
+        gx = nullptr;
+      }
+}
+
 void free_work(Work& w) {
+  drop_graphs(w);
   auto f = [](void* p) {
     if (p) (void)hipFree(p);
   };
@@ -295,9 +307,6 @@ void free_ctx(qcd_ctx* c) {
   f(c->md_partial);
   f(c->logdet);
   if (c->act_host) (void)hipHostFree(c->act_host);
-  for (auto& row : c->iter_graph)
-    for (auto& gx : row)
-      if (gx) (void)hipGraphExecDestroy(gx);
   if (c->cap) (void)hipStreamDestroy(c->cap);
 }
 
@@ -638,24 +647,23 @@ int launch_iter(qcd_ctx* c, bool mixed, int j) {
   return QCD_OK;
 }
 
-// A solve that failed (QCD_ENAN) leaves iterations on the stream, so a graph
-// goes only once the stream has run what was launched.
+// A solve that failed (QCD_ENAN) leaves iterations on the stream, so graphs
+// go only once the stream has run what was launched.
 int drop_graphs(qcd_ctx* c) {
-  bool waited = false;
-  for (auto& row : c->iter_graph)
-    for (auto& gx : row)
-      if (gx) {
-        if (!waited) HIPCHK(hipStreamSynchronize(c->stream));
-        waited = true;
-        (void)hipGraphExecDestroy(gx);
-        gx = nullptr;
-      }
+  bool any = false;
+  for (const Work* w : {&c->w1, &c->wm})
+    for (const auto& row : w->iter_graph)
+      for (const auto& gx : row) any = any || gx != nullptr;
+  if (!any) return QCD_OK;
+  HIPCHK(hipStreamSynchronize(c->stream));
+  drop_graphs(c->w1);
+  drop_graphs(c->wm);
   return QCD_OK;
 }
 
 // Capture one iteration on the private stream into an executable graph.
 int capture_iter(qcd_ctx* c, bool mixed, int j) {
-  hipGraphExec_t& gx = c->iter_graph[mixed ? 1 : 0][j];
+  hipGraphExec_t& gx = c->w->iter_graph[mixed ? 1 : 0][j];
   if (gx) return QCD_OK;
   const hipStream_t saved = c->stream;
   HIPCHK(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
@@ -682,7 +690,7 @@ int enqueue_iter(qcd_ctx* c, Pipe& pp, bool mixed) {
   const int j = (int)(pp.seq % c->x_defer);
   if (c->use_graph && c->w->nr == 1) {
     QCHK(capture_iter(c, mixed, j));
-    HIPCHK(hipGraphLaunch(c->iter_graph[mixed ? 1 : 0][j], c->stream));
+    HIPCHK(hipGraphLaunch(c->w->iter_graph[mixed ? 1 : 0][j], c->stream));
   } else {
     QCHK(launch_iter(c, mixed, j));
   }
@@ -1190,6 +1198,7 @@ int use_multi(qcd_ctx* c, int n) {
   if ((long long)c->g.stride * room * 48 >= (1LL << 32))
     return fail(QCD_EINVAL, "too many interleaved right-hand sides for this lattice volume");
   if (c->wm.st == nullptr || c->wm_alloc < room) {
+    if (c->wm.st != nullptr) HIPCHK(hipStreamSynchronize(c->stream));  // a failed solve leaves iterations there
     free_work(c->wm);
     c->wm_alloc = 0;
     QCHK(alloc_work(c->g, c->wm, room, false));

@@ -35,3 +35,22 @@ def test_option_after_a_failed_solve(lat, prec):
             lat.solve(bad, prec=prec, pipeline_depth=16)
     lat.set_option(capi.QCD_OPT_GRAPH, 0)
     assert torch.equal(lat.solve(b, prec=prec)[0], x0)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_each_work_set_has_its_own_graphs(lat, prec):
+    """qcd_solve and qcd_solve_multi with one source work on different buffers; a set that
+    grows for more sources moves its own."""
+    bs = to_dev(np.stack([synth.gaussian_source(DIMS, 2, k) for k in range(5)]))
+    one = [lat.solve(bs[k], prec=prec)[0] for k in range(3)]
+    five = lat.solve_multi(bs, prec=prec)[0]
+    fresh = Lattice(DIMS, 0.12, 1.0)  # its set for several sources starts with one
+    fresh.load_gauge(lat.store_gauge())
+    fresh.set_option(capi.QCD_OPT_GRAPH, 1)
+    for _ in range(2):
+        for k in range(3):
+            assert torch.equal(fresh.solve(bs[k], prec=prec)[0], one[k])
+            x, st = fresh.solve_multi(bs[k:k + 1].contiguous(), prec=prec)
+            assert torch.equal(x[0], one[k]) and st[0]["restarts"] == 0
+        assert torch.equal(fresh.solve_multi(bs, prec=prec)[0], five)
+    fresh.close()
