@@ -310,6 +310,20 @@ void free_ctx(qcd_ctx* c) {
   if (c->cap) (void)hipStreamDestroy(c->cap);
 }
 
+// A solve that failed (QCD_ENAN) leaves iterations on the stream, so graphs
+// go only once the stream has run what was launched.
+int drop_graphs(qcd_ctx* c) {
+  bool any = false;
+  for (const Work* w : {&c->w1, &c->wm})
+    for (const auto& row : w->iter_graph)
+      for (const auto& gx : row) any = any || gx != nullptr;
+  if (!any) return QCD_OK;
+  HIPCHK(hipStreamSynchronize(c->stream));
+  drop_graphs(c->w1);
+  drop_graphs(c->wm);
+  return QCD_OK;
+}
+
 // the site term of k2 reads the compact A_ee where the clover term has its form
 bool use_compact(const qcd_ctx* c) { return c->compact_clover == 1 && c->compact_ok; }
 int check_ctx(qcd_ctx* c) {
@@ -644,20 +658,6 @@ int launch_iter(qcd_ctx* c, bool mixed, int j) {
     for (int m = 0; m < n; ++m) p[m] = c->h(qcd_ctx::hpslot(m));
     HIPCHK(launch_xp_update_h(c->w->gv, c->w->nr, c->w->st, c->f32(), p, j, n, c->h(H_R), kXpBlock, c->stream));
   }
-  return QCD_OK;
-}
-
-// A solve that failed (QCD_ENAN) leaves iterations on the stream, so graphs
-// go only once the stream has run what was launched.
-int drop_graphs(qcd_ctx* c) {
-  bool any = false;
-  for (const Work* w : {&c->w1, &c->wm})
-    for (const auto& row : w->iter_graph)
-      for (const auto& gx : row) any = any || gx != nullptr;
-  if (!any) return QCD_OK;
-  HIPCHK(hipStreamSynchronize(c->stream));
-  drop_graphs(c->w1);
-  drop_graphs(c->wm);
   return QCD_OK;
 }
 
@@ -1071,7 +1071,9 @@ static int clover_done(qcd_ctx* c) {
   c->clover_ready = false;
   QCHK(clover_copy32(c));
   HIPCHK(hipStreamSynchronize(c->stream));
-  c->compact_ok = c->status_host[1] == 0;
+  const bool compact_ok = c->status_host[1] == 0;
+  if (compact_ok != c->compact_ok) QCHK(drop_graphs(c));  // their k2 reads the other form of A_ee
+  c->compact_ok = compact_ok;
   if (c->status_host[0] != 0) return fail(QCD_ECLOVER, "an odd-site clover block is not positive definite");
   c->clover_ready = true;
   return QCD_OK;

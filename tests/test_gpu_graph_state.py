@@ -54,3 +54,26 @@ def test_each_work_set_has_its_own_graphs(lat, prec):
             assert torch.equal(x[0], one[k]) and st[0]["restarts"] == 0
         assert torch.equal(fresh.solve_multi(bs, prec=prec)[0], five)
     fresh.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_clover_form_changes_between_solves(lat, prec):
+    """A built clover term has the compact form, a loaded one need not: the iterations captured
+    for one read other fields than the other's."""
+    b = to_dev(synth.gaussian_source(DIMS, 2, 0))
+    built = lat.get_clover()[0]
+    other = built.clone()
+    other[:, 0, 0] += 0.4  # not 2 minus the lower spin's entry
+    ref, ref_stats = [], []
+    for A in (built, other):
+        lat.load_clover(A)
+        x, st = lat.solve(b, prec=prec)
+        ref.append(x)
+        ref_stats.append(st)
+    assert float((ref[0] - ref[1]).abs().max()) > 1e-2
+    lat.set_option(capi.QCD_OPT_GRAPH, 1)
+    for k in (0, 1, 0, 1):
+        lat.load_clover((built, other)[k])
+        x, st = lat.solve(b, prec=prec)
+        assert torch.equal(x, ref[k]), k
+        assert st["iters"] == ref_stats[k]["iters"] and st["restarts"] == ref_stats[k]["restarts"]
