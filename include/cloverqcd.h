@@ -319,7 +319,8 @@ typedef struct {
  * U_dev: complex128 [V][4][3][3], in/out.  P_dev: float64 [V][4][8], in/out.
  * xi_dev: complex128 [n_steps][Vh][4][3] on even sites.  actions (host, may
  * be NULL): float64 [n_steps][3] receives (S_f, S_g, S_det) at each step's
- * force evaluation, unweighted.  stats (may be NULL): the sum over the
+ * force evaluation, unweighted; of a trajectory that stops with an error,
+ * those of the steps before the one that failed.  stats (may be NULL): the sum over the
  * step's solves; seconds of the whole trajectory.  Waits for its work.  On
  * return the context holds the final U (and for n_f > 0 its clover term).
  * QCD_ENOCONV if any solve missed tol (the trajectory still completes). */

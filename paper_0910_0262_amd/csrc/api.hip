@@ -1508,9 +1508,25 @@ int qcd_clover_det_action_force(qcd_ctx* c, double* S, void* G_dev, double* F_de
   return QCD_OK;
 }
 
+// Steps of a trajectory: all before `done` have run or are on the stream; the
+// actions of step k from `first` on wait in act_host's slot k mod kActRing.
+struct MdSteps {
+  int first = 0, done = 0;
+};
+
+// Hands out the actions that wait, once the stream has been waited for.
+static void md_actions(qcd_ctx* c, const qcd_md_params* md, MdSteps& m, double* actions) {
+  for (; m.first < m.done; ++m.first) {
+    const double* a = c->act_host + 3 * (m.first % kActRing);
+    actions[3 * m.first] = a[0];
+    actions[3 * m.first + 1] = md->beta * a[1];
+    actions[3 * m.first + 2] = -2.0 * a[2];
+  }
+}
+
 // The steps of qcd_md_trajectory.
 static int md_run(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* P_dev, const void* xi_dev,
-                  const qcd_solver_params* p, double* actions, CgCounters& cnt, int* conv_all) {
+                  const qcd_solver_params* p, double* actions, MdSteps& m, CgCounters& cnt, int* conv_all) {
   const Geom& g = c->g;
   const double dt = md->dt, wf = 0.5 * md->n_f;
   const bool ferm = wf != 0.0, det = md->clover_det == 1 && ferm, reunit = md->reunitarize == 1;
@@ -1529,10 +1545,9 @@ static int md_run(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* P_de
   c->gauge_loaded = true;
   c->clover_ready = false;
   if (!ferm) HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, false, false, LinkCopies{}, c->stream));
-  int first = 0;  // the step in slot 0 of act_host
   for (int k = 0; k < md->n_steps; ++k) {
     const bool last = k == md->n_steps - 1;
-    const int slot = k - first;
+    const int slot = k % kActRing;
     c->act_host[3 * slot] = c->act_host[3 * slot + 1] = c->act_host[3 * slot + 2] = 0.0;
     if (ferm) {
       if (h1 != 0.0) HIPCHK(launch_move_links(g, c->u18, P_dev, h1, false, false, draw_copies, c->stream));
@@ -1565,17 +1580,10 @@ static int md_run(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* P_de
     const LinkCopies end_copies = last ? c->all_copies() : (h1 == 0.0 ? draw_copies : LinkCopies{});
     HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, reunit, !ferm && !last, end_copies, c->stream));
     c->clover_ready = false;
+    m.done = k + 1;
     if (actions && (last || slot == kActRing - 1)) {
       HIPCHK(hipStreamSynchronize(c->stream));
-      for (int j = first; j <= k; ++j) {
-        const double* a = c->act_host + 3 * (j - first);
-        actions[3 * j] = a[0];
-        actions[3 * j + 1] = md->beta * a[1];
-        actions[3 * j + 2] = -2.0 * a[2];
-      }
-      first = k + 1;
-    } else if (slot == kActRing - 1) {
-      first = k + 1;
+      md_actions(c, md, m, actions);
     }
   }
   HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
@@ -1602,8 +1610,13 @@ int qcd_md_trajectory(qcd_ctx* c, const qcd_md_params* md, void* U_dev, double* 
   const auto t0 = std::chrono::steady_clock::now();
   CgCounters cnt;
   int conv_all = QCD_OK;
-  const int rc = md_run(c, md, U_dev, P_dev, xi_dev, p, actions, cnt, &conv_all);
-  if (rc != QCD_OK) return md_failed(c, rc);
+  MdSteps m;
+  const int rc = md_run(c, md, U_dev, P_dev, xi_dev, p, actions, m, cnt, &conv_all);
+  if (rc != QCD_OK) {
+    // the steps before the one that failed have their actions
+    if (actions && m.first < m.done && hipStreamSynchronize(c->stream) == hipSuccess) md_actions(c, md, m, actions);
+    return md_failed(c, rc);
+  }
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   if (stats) {
     if (ferm) {
