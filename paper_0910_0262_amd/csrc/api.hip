@@ -1394,8 +1394,9 @@ static int md_failed(qcd_ctx* c, int rc) {
   return rc;
 }
 
+// posted: whether the fermion action is on its way to act_host.
 static int hmd_step_run(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* xi_dev,
-                        const qcd_solver_params* p, CgCounters& cnt, int* conv) {
+                        const qcd_solver_params* p, CgCounters& cnt, int* conv, bool* posted) {
   const Geom& g = c->g;
   QCHK(ensure_force_buffers(c));
   // two flavours per pseudofermion at N_f = 2: the R algorithm draws the
@@ -1414,6 +1415,7 @@ static int hmd_step_run(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const
   out.p_user = P_dev;
   out.dt = dt;
   QCHK(force_core(c, p, 0, cnt, conv, out));
+  *posted = true;
   HIPCHK(launch_move_links(g, c->u18, P_dev, 0.5 * dt, false, false, c->all_copies(), c->stream));
   HIPCHK(launch_unpack_gauge(g, c->u18, (double2*)U_dev, c->stream));
   return qcd_build_clover(c);
@@ -1428,9 +1430,10 @@ int qcd_hmd_step(qcd_ctx* c, double dt, void* U_dev, double* P_dev, const void* 
   const auto t0 = std::chrono::steady_clock::now();
   CgCounters cnt;
   int conv = QCD_OK;
-  const int rc = hmd_step_run(c, dt, U_dev, P_dev, xi_dev, p, cnt, &conv);
+  bool posted = false;
+  const int rc = hmd_step_run(c, dt, U_dev, P_dev, xi_dev, p, cnt, &conv, &posted);
+  if (S && posted && hipStreamSynchronize(c->stream) == hipSuccess) *S = c->act_host[0];
   if (rc != QCD_OK) return md_failed(c, rc);
-  if (S) *S = c->act_host[0];  // the clover build waited for the stream
   const double seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   fill_stats(c, cnt, p, seconds, -1.0, stats);
   if (conv != QCD_OK) return fail(QCD_ENOCONV, "force solve reached max_iter without meeting tol");
