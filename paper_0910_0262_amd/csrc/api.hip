@@ -1523,7 +1523,7 @@ static void md_actions(qcd_ctx* c, const qcd_md_params* md, MdSteps& m, double* 
     const double* a = c->act_host + 3 * (m.first % kActRing);
     actions[3 * m.first] = a[0];
     actions[3 * m.first + 1] = md->beta * a[1];
-    actions[3 * m.first + 2] = -2.0 * a[2];
+    actions[3 * m.first + 2] = 0.0 - 2.0 * a[2];  // 0, not -0, where there is no determinant
   }
 }
 

@@ -71,3 +71,13 @@ def test_action_of_a_step_that_ends_beyond_the_clover_term():
     ref = O.action_and_gradient(mid_links, kappa, csw, phi, tol=1e-13)[0]
     assert abs(s.value - ref) < 1e-9 * abs(ref)
     lat.close()
+
+
+def test_actions_left_out_are_plus_zero():
+    u, p = to_dev(synth.random_su3_field(DIMS, 0.3, 4)), to_dev(synth.momenta(DIMS, 4))
+    lat = Lattice(DIMS, 0.12, 1.0)
+    acts, _ = lat.md_trajectory(u, p, None, DT, 2, beta=BETA, n_f=0.0)
+    assert [str(a[k]) for a in acts for k in (0, 2)] == ["0.0"] * 4
+    acts, _ = lat.md_trajectory(u, p, to_dev(synth.heatbath_xi(DIMS, 4))[None], DT, 1, n_f=2.0, clover_det=False)
+    assert [str(a) for a in acts[0][1:]] == ["0.0"] * 2
+    lat.close()
