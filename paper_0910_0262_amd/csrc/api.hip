@@ -64,6 +64,7 @@ constexpr int kActRing = 64;
 // and the trajectory; a second set is allocated for multi-source solves.
 struct Work {
   int nr = 1;
+  int block = 64;  // workgroup of the stencils and reductions
   Geom gv;  // Vh and stride of all right-hand sides together (for the BLAS kernels)
   double2* vec[NSLOT] = {};
   uint4* hv[NHSLOT] = {};
@@ -79,6 +80,9 @@ struct Work {
   hipGraphExec_t iter_graph[2][4] = {};
 };
 
+// Partials per right-hand side up to which the dagger k1 finishes alpha itself.
+constexpr int kFuseFinPartials = 1024;
+
 // Workgroup of the multi-source kernels on n elements (sites times right-hand
 // sides).  256 gives a quarter of the partial sums, but while all wavefronts
 // are resident at once (up to 2048, eight to a CU) a launch takes as long as
@@ -92,13 +96,20 @@ struct Work {
 // 8 sources, 8 against 7 wavefronts: mixed [4882] with 256, 5040 with 64; FP64
 // [8576] and 8430), and with more wavefronts 256 leads (16^4, 5 sources
 // [13388] | 13672 | 13607, 6 sources [14215] | 15634 | 14553).
-int multi_block(int n) {
+// From 1025 to 1280 wavefronts 64 threads save a wavefront on the fullest CU (5
+// instead of 6 with 128), but leave more partial sums than the dagger k1
+// finishes, so alpha gets a launch of its own.  FP64 gains all the same, mixed
+// does not: 12^3x16, 5 sources FP64 7637 | 6627 | [6216], mixed 4834 | [4596] |
+// 4701; 16^3x8, 5 sources 7076 | 6137 | [5783] and 4470 | [4256] | 4334; 8^2x16^2,
+// 9 sources 7781 | 6898 | [6515] and 4865 | [4632] | 4779.
+int multi_block(int n, bool mixed) {
   constexpr int kCus = 256;
   const int waves = blocks_for(n, 64);
   if (waves > 8 * kCus) return 256;
   const int most256 = 4 * blocks_for(blocks_for(n, 256), kCus);
   int best = 256, least = most256;
   for (int b = 128; b >= 64; b /= 2) {
+    if (mixed && blocks_for(n, b) > kFuseFinPartials) break;
     const int most = (b / 64) * blocks_for(blocks_for(n, b), kCus);
     if (most < least && 4 * most <= 3 * most256) {
       best = b;
@@ -175,7 +186,7 @@ struct qcd_ctx {
   // single-source work; multi_block() for several sources: on large lattices
   // 256, where FP64 solves are about 1 % faster than at 64 and mixed ones equal
   // (the x/p update keeps 64 threads, kXpBlock).
-  int block() const { return block_opt ? block_opt : (w->nr > 1 ? multi_block(w->gv.Vh) : 64); }
+  int block() const { return block_opt ? block_opt : w->block; }
   SpF64 f64(int s) const { return SpF64{w->vec[s], w->gv.stride}; }
   SpRef ref64(int s) const { return SpRef{SP_F64, w->vec[s], nullptr}; }
   SpRef refh(int s) const { return SpRef{SP_H, w->hv[s], w->hs[s]}; }
@@ -613,8 +624,6 @@ int init_recurrence(qcd_ctx* c, double tol, double delta, int max_iter, int mixe
   return QCD_OK;
 }
 
-// Partials per right-hand side up to which the dagger k1 finishes alpha itself.
-constexpr int kFuseFinPartials = 1024;
 // Workgroup size of the x/p update, which leaves no partial sums: 64 threads
 // streamed faster than 256 for several right-hand sides.
 constexpr int kXpBlock = 64;
@@ -1192,7 +1201,7 @@ struct WorkGuard {
 // Make the multi-source work set hold n right-hand sides.  Memory and the
 // limit on the volume are those of the next power of two, so that requests
 // for a few more or fewer reuse one allocation.
-int use_multi(qcd_ctx* c, int n) {
+int use_multi(qcd_ctx* c, int n, int prec) {
   int room = 1;
   while (room < n) room *= 2;
   // the stencils address a chunk element with a 32-bit byte offset (16-byte
@@ -1211,6 +1220,7 @@ int use_multi(qcd_ctx* c, int n) {
   w.gv = c->g;
   w.gv.Vh = c->g.Vh * n;
   w.gv.stride = c->g.stride * n;
+  w.block = n > 1 ? multi_block(w.gv.Vh, prec == QCD_MIXED) : 64;
   return QCD_OK;
 }
 
@@ -1299,7 +1309,7 @@ int qcd_solve_multi(qcd_ctx* c, const qcd_solver_params* p, int n_rhs, const voi
   QCHK(need_clover(c));
   const auto t0 = std::chrono::steady_clock::now();
   // a set allocated for more right-hand sides serves fewer (its buffers are larger)
-  QCHK(use_multi(c, n_rhs));
+  QCHK(use_multi(c, n_rhs, p->prec));
   Work& w = c->wm;
   WorkGuard wg(c, &w);
   HIPCHK(launch_pack_spinor_multi(c->g, n_rhs, (const double2*)b_dev, c->f64(V_B_E), c->f64(V_B_O), c->stream));
@@ -1722,7 +1732,7 @@ int qcd_time_stencil(qcd_ctx* c, int prec, int n, double* ms) {
 int qcd_time_stencil_multi(qcd_ctx* c, int prec, int n_rhs, int n, double* ms) {
   QCHK(check_time_args(c, prec, n, ms));
   if (n_rhs < 1 || n_rhs > QCD_MAX_RHS) return fail(QCD_EINVAL, "n_rhs must lie in [1, 16]");
-  QCHK(use_multi(c, n_rhs));
+  QCHK(use_multi(c, n_rhs, prec));
   WorkGuard wg(c, &c->wm);
   const int f[4] = {V_P, V_T, V_Q, V_AUX}, h[4] = {H_P, H_T, H_Q, H_R};
   return time_stencil_impl(c, prec, n, ms, f, h);
