@@ -492,7 +492,7 @@ double* fold_area(const qcd_ctx* c) {
 
 // |x|^2 of each right-hand side of an FP64 vector to norm_host[16 slot + r]
 int post_norm2(qcd_ctx* c, int s, int slot) {
-  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->ref64(s), c->w->partial, c->block(), c->stream));
+  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->f64(s), c->w->partial, c->block(), c->stream));
   HIPCHK(launch_fin_sum(c->norm_dev + 16 * slot, c->w->partial, nblocks(c), c->w->nr, fold_area(c), c->stream));
   return QCD_OK;
 }
@@ -617,7 +617,7 @@ int recompute_residual(qcd_ctx* c, int restart, CgState* posted, int nclear = 0)
 
 // Starts the recurrence; its first state is posted with *tag.
 int init_recurrence(qcd_ctx* c, double tol, double delta, int max_iter, int mixed, unsigned int* tag) {
-  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->ref64(V_RHS), c->w->partial, c->block(), c->stream));
+  HIPCHK(launch_norm2(c->w->gv, c->w->nr, c->f64(V_RHS), c->w->partial, c->block(), c->stream));
   HIPCHK(launch_fin_init(c->w->st, c->w->partial, nblocks(c), c->w->nr, fold_area(c), tol, delta, max_iter, mixed,
                          c->w->post_ctr, c->w->mbox_dev, kRing, c->stream));
   *tag = next_tag(c);
@@ -739,8 +739,8 @@ int cg_fp64(qcd_ctx* c, const qcd_solver_params* p, bool use_x0, CgCounters& cnt
     HIPCHK(launch_p_restart_f64(c->w->gv, c->w->nr, c->w->st, c->f64(V_P), c->f64(V_R), B, c->stream));
   } else {
     HIPCHK(launch_zero(c->w->gv, c->ref64(V_X), B, c->stream));
-    HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->ref64(V_R), B, c->stream));
-    HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->ref64(V_P), B, c->stream));
+    HIPCHK(launch_convert(c->w->gv, c->f64(V_RHS), c->ref64(V_R), B, c->stream));
+    HIPCHK(launch_convert(c->w->gv, c->f64(V_RHS), c->ref64(V_P), B, c->stream));
     // the first iterations do not wait for the start's state (nothing of
     // them runs where it was final)
     while (pp.seq < depth) QCHK(enqueue_iter(c, pp, false));
@@ -795,8 +795,8 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
   QCHK(init_recurrence(c, p->tol, p->delta_reliable, p->max_iter, 1, &start));
   HIPCHK(launch_zero(c->w->gv, c->ref64(V_X), B, c->stream));
   HIPCHK(launch_zero(c->w->gv, SpRef{SP_F32, c->w->x32, nullptr}, B, c->stream));
-  HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->refh(H_R), B, c->stream));
-  HIPCHK(launch_convert(c->w->gv, c->ref64(V_RHS), c->refh(H_P), B, c->stream));
+  HIPCHK(launch_convert(c->w->gv, c->f64(V_RHS), c->refh(H_R), B, c->stream));
+  HIPCHK(launch_convert(c->w->gv, c->f64(V_RHS), c->refh(H_P), B, c->stream));
   const int depth = pipeline_depth(p);
   Pipe pp;
   while (pp.seq < depth) QCHK(enqueue_iter(c, pp, true));  // as in cg_fp64
@@ -835,7 +835,7 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
       const int q = fold_x(c, pp);
       if (q < 0) return q;
       QCHK(recompute_residual(c, 0, nullptr, q));
-      HIPCHK(launch_convert(c->w->gv, c->ref64(V_R), c->refh(H_R), B, c->stream));
+      HIPCHK(launch_convert(c->w->gv, c->f64(V_R), c->refh(H_R), B, c->stream));
       cnt.mdagm += 1;
       cnt.ru += 1;
       ru_barrier = pp.seq;

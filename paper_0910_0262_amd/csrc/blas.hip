@@ -213,8 +213,7 @@ hipError_t launch_unpack_clover(const Geom& g, const double2* clov, double2* use
 
 // ------------------------------------------------------------------ reductions
 // gv: Vh and stride of all interleaved right-hand sides together.
-template <class F>
-__global__ void __launch_bounds__(256) norm2_k(Geom gv, RhsDiv d, F x, double* partial) {
+__global__ void __launch_bounds__(256) norm2_k(Geom gv, RhsDiv d, SpF64 x, double* partial) {
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   const int i = blk * blockDim.x + threadIdx.x;
   double n = 0.0;
@@ -238,16 +237,8 @@ __global__ void __launch_bounds__(256) dot_re_k(Geom gv, RhsDiv d, SpF64 a, SpF6
   }
   block_sum_store_seg(n, partial, blk, gridDim.x, d);
 }
-hipError_t launch_norm2(const Geom& gv, int nr, SpRef x, double* partial, int block, hipStream_t s) {
-  const int nb = blocks_for(gv.Vh, block);
-  if (x.kind == SP_F64)
-    hipLaunchKernelGGL(norm2_k<SpF64>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpF64{(double2*)x.p, gv.stride}, partial);
-  else if (x.kind == SP_F32)
-    hipLaunchKernelGGL(norm2_k<SpF32>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpF32{(float4*)x.p, gv.stride}, partial);
-  else if (x.kind == SP_H)
-    hipLaunchKernelGGL(norm2_k<SpH>, dim3(nb), dim3(block), 0, s, gv, rhs_div(nr), SpH{(uint4*)x.p, x.s, gv.stride}, partial);
-  else
-    return hipErrorInvalidValue;
+hipError_t launch_norm2(const Geom& gv, int nr, SpF64 x, double* partial, int block, hipStream_t s) {
+  hipLaunchKernelGGL(norm2_k, dim3(blocks_for(gv.Vh, block)), dim3(block), 0, s, gv, rhs_div(nr), x, partial);
   return hipGetLastError();
 }
 hipError_t launch_dot_re(const Geom& gv, int nr, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s) {
@@ -619,8 +610,8 @@ hipError_t launch_ru_accum(const Geom& gv, int nr, const CgState* st, SpF64 xhi,
 }
 
 // ------------------------------------------------------------------ conversions
-template <class FS, class FD>
-__global__ void __launch_bounds__(256) convert_k(Geom g, FS src, FD dst) {
+template <class FD>
+__global__ void __launch_bounds__(256) convert_k(Geom g, SpF64 src, FD dst) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.Vh) return;
   Spinor<double> vd;
@@ -628,7 +619,7 @@ __global__ void __launch_bounds__(256) convert_k(Geom g, FS src, FD dst) {
   if constexpr (std::is_same_v<FD, SpF64>) {
     store(dst, i, vd);
   } else {
-    // round to float32 first: the binary16 and FP32 encoders work on float32 values
+    // round to float32 first: the binary16 encoder works on float32 values
     Spinor<float> vf;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -637,24 +628,15 @@ __global__ void __launch_bounds__(256) convert_k(Geom g, FS src, FD dst) {
     store(dst, i, vf);
   }
 }
-template <class FS>
-static hipError_t convert_to(const Geom& g, FS src, SpRef dst, int block, hipStream_t s) {
+hipError_t launch_convert(const Geom& g, SpF64 src, SpRef dst, int block, hipStream_t s) {
   const int nb = blocks_for(g.Vh, block);
   if (dst.kind == SP_F64)
-    hipLaunchKernelGGL((convert_k<FS, SpF64>), dim3(nb), dim3(block), 0, s, g, src, SpF64{(double2*)dst.p, g.stride});
-  else if (dst.kind == SP_F32)
-    hipLaunchKernelGGL((convert_k<FS, SpF32>), dim3(nb), dim3(block), 0, s, g, src, SpF32{(float4*)dst.p, g.stride});
+    hipLaunchKernelGGL(convert_k<SpF64>, dim3(nb), dim3(block), 0, s, g, src, SpF64{(double2*)dst.p, g.stride});
   else if (dst.kind == SP_H)
-    hipLaunchKernelGGL((convert_k<FS, SpH>), dim3(nb), dim3(block), 0, s, g, src, SpH{(uint4*)dst.p, dst.s, g.stride});
+    hipLaunchKernelGGL(convert_k<SpH>, dim3(nb), dim3(block), 0, s, g, src, SpH{(uint4*)dst.p, dst.s, g.stride});
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
-}
-hipError_t launch_convert(const Geom& g, SpRef src, SpRef dst, int block, hipStream_t s) {
-  if (src.kind == SP_F64) return convert_to(g, SpF64{(double2*)src.p, g.stride}, dst, block, s);
-  if (src.kind == SP_F32) return convert_to(g, SpF32{(float4*)src.p, g.stride}, dst, block, s);
-  if (src.kind == SP_H) return convert_to(g, SpH{(uint4*)src.p, src.s, g.stride}, dst, block, s);
-  return hipErrorInvalidValue;
 }
 
 template <class F>
@@ -671,8 +653,6 @@ hipError_t launch_zero(const Geom& g, SpRef x, int block, hipStream_t s) {
     hipLaunchKernelGGL(zero_k<SpF64>, dim3(nb), dim3(block), 0, s, g, SpF64{(double2*)x.p, g.stride});
   else if (x.kind == SP_F32)
     hipLaunchKernelGGL(zero_k<SpF32>, dim3(nb), dim3(block), 0, s, g, SpF32{(float4*)x.p, g.stride});
-  else if (x.kind == SP_H)
-    hipLaunchKernelGGL(zero_k<SpH>, dim3(nb), dim3(block), 0, s, g, SpH{(uint4*)x.p, x.s, g.stride});
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -109,7 +109,6 @@ __device__ __forceinline__ void md_emit(const MdOut& o, const double2* gin, MdLd
     for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int c = 0; c < 3; ++c) G.m[r][c] = G.m[r][c] + ti(conj(mt.m[c][r]));
-    if (o.g_int != nullptr && lane < n_live) store_mat(o.g_int + field, g.stride, s.cb, G);
     if (o.g_user != nullptr) {
 #pragma unroll
       for (int k = 0; k < 9; ++k) lds.v[lane * 9 + k] = make_double2(G.m[k / 3][k % 3].re, G.m[k / 3][k % 3].im);

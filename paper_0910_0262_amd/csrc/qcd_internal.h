@@ -192,7 +192,7 @@ hipError_t launch_unpack_clover(const Geom& g, const double2* clov, double2* use
                                 hipStream_t s);
 // Spinor BLAS: gv is the geometry with Vh and stride scaled by the number of
 // right-hand sides (nr); per-rhs states and segmented partial sums.
-hipError_t launch_norm2(const Geom& gv, int nr, SpRef x, double* partial, int block, hipStream_t s);
+hipError_t launch_norm2(const Geom& gv, int nr, SpF64 x, double* partial, int block, hipStream_t s);
 hipError_t launch_dot_re(const Geom& gv, int nr, SpF64 a, SpF64 b, double* partial, int block, hipStream_t s);
 // Finalisation kernels: one workgroup per right-hand side (nr of them), each
 // summing its n partials and updating its own state.  With kFoldMin or more
@@ -222,7 +222,7 @@ hipError_t launch_p_restart_f64(const Geom& gv, int nr, const CgState* st, SpF64
 // x_hi += x_lo + the first q directions p[0 .. q-1] of the unfinished cycle; x_lo = 0
 hipError_t launch_ru_accum(const Geom& gv, int nr, const CgState* st, SpF64 xhi, SpF32 xlo, const SpH* p, int q,
                            int block, hipStream_t s);
-hipError_t launch_convert(const Geom& g, SpRef src, SpRef dst, int block, hipStream_t s);
+hipError_t launch_convert(const Geom& g, SpF64 src, SpRef dst, int block, hipStream_t s);
 hipError_t launch_zero(const Geom& g, SpRef x, int block, hipStream_t s);
 // the caller's checkerboard array to the binary16 field and back, as a
 // conversion through an FP64 field would
@@ -256,11 +256,10 @@ hipError_t launch_clover_copy32(const Geom& g, const double2* clov, const double
                                 hipStream_t s);
 
 // ---- force.hip
-// Where a force pass puts G (dS/dRe U + i dS/dIm U): any of the accumulator
-// [mu][par][9][stride], the caller's G [V][4][9] and su(3) force [V][4][8],
-// and the caller's momenta [V][4][8], which take P -= dt F.
+// Where a force pass puts G (dS/dRe U + i dS/dIm U): any of the caller's G
+// [V][4][9] and su(3) force [V][4][8], and the caller's momenta [V][4][8],
+// which take P -= dt F.
 struct MdOut {
-  double2* g_int = nullptr;
   double2* g_user = nullptr;
   double* f_user = nullptr;
   double* p_user = nullptr;
