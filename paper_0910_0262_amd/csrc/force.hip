@@ -559,6 +559,7 @@ force_clover_k(MdGeom m, const double2* __restrict__ u18, const double2* __restr
 hipError_t launch_force_clover(const Geom& g, const double2* u18, const double2* xi, double coef, double coef_g,
                                const double2* gin, const MdOut& o, double* partial, hipStream_t s) {
   const dim3 grid(md_link_blocks(g)), block(64);
+  if (coef_g != 0.0 && partial == nullptr) return hipErrorInvalidValue;
   if (coef_g != 0.0)
     hipLaunchKernelGGL(force_clover_k<true>, grid, block, 0, s, md_geom(g), u18, xi, coef, coef_g, gin, o, partial);
   else
@@ -572,8 +573,8 @@ hipError_t launch_force_clover(const Geom& g, const double2* u18, const double2*
 // links, each wavefront one nu: at 16^4, where there are few wavefronts, 67
 // instead of 77 us per call with a wavefront per plane and both its links, and
 // 158 with a work-item per link and separate action and output kernels; at
-// 32^3x64 1.70, 1.66 and 3.68 ms (the start 1.75 ms of it in the staples alone,
-// 0.73 in the action and 1.23 in the output).
+// 32^3x64 1.70, 1.66 and 3.68 ms (of the last, 1.75 in the staples alone, 0.73
+// in the action and 1.23 in the output).
 template <bool ACTION>
 __global__ void __launch_bounds__(192) gauge_force_k(MdGeom m, const double2* __restrict__ u18, double coef,
                                                      const double2* gin, MdOut o, double* __restrict__ partial) {
@@ -610,8 +611,9 @@ hipError_t launch_gauge_force(const Geom& g, const double2* u18, double coef, co
   return hipGetLastError();
 }
 
-// The action alone, from the up staples alone: the partial sums of the force
-// passes, bit for bit.  One work-item per site, four partial sums per workgroup.
+// The action alone, from the up staples alone: the partial sums of
+// gauge_force_k, bit for bit (force_clover_k adds a link's planes before it
+// sums over links).  One work-item per site, four partial sums per workgroup.
 __global__ void __launch_bounds__(64) plaquette_k(MdGeom m, const double2* __restrict__ u18, double* partial) {
   const int w = xcd_block(blockIdx.x, gridDim.x), par = w & 1;
   const int j = ((w >> 1) << 6) + threadIdx.x;

@@ -178,7 +178,7 @@ hipError_t launch_pack_spinor_multi(const Geom& g, int n, const double2* user, S
 hipError_t launch_unpack_spinor_multi(const Geom& g, int n, SpF64 e, SpF64 o, double2* user, hipStream_t s);
 // Copies of the links the stencils read, any of them null where it is not
 // wanted.  u12: FP64 rows 0, 1; uh: binary16 rows 0, 1; uh18: all nine binary16
-// entries (16 * stride uint4 chunks followed by 8 * stride 32-bit chunks).
+// entries, by rows (LinkH18).
 struct LinkCopies {
   double2* u12 = nullptr;
   uint2* uh = nullptr;
@@ -277,7 +277,8 @@ hipError_t launch_clover_xi(const Geom& g, SpF64 ell_e, SpF64 ell_o, SpF64 rho_e
                             double w_o, const double2* cinv, double w_det, double2* xi, hipStream_t s);
 // The force passes start from the accumulator gin (null: zero).  coef_g != 0
 // adds the Wilson gauge force (weight coef_g, as launch_gauge_force) in the
-// clover pass; partial (may be null) then receives the action's partial sums.
+// clover pass, which then leaves the action's partial sums in partial (refused
+// if null); launch_gauge_force leaves them where partial is not null.
 hipError_t launch_force_clover(const Geom& g, const double2* u18, const double2* xi, double coef, double coef_g,
                                const double2* gin, const MdOut& o, double* partial, hipStream_t s);
 hipError_t launch_gauge_force(const Geom& g, const double2* u18, double coef, const double2* gin, const MdOut& o,
