@@ -176,7 +176,7 @@ __device__ __forceinline__ void hop_dir(const A& a, int i, int r, const int x[4]
 // mean square error 3.7e-8 of the result; with FMA chains 5.3e-8).
 // Vector instructions per wavefront 1435 -> 1067 (k1) and 1809 -> 1143 (k2).
 // Mhat^dag Mhat with 4, 8 sources on 16^4: 48 -> 40, 72 -> 64 us; 24^3x48: 297 ->
-// 267, 534 -> 517; 32^3x64: 875 -> 885, 1612 -> 1580 (4.8 TB/s in k1, 5.5 in k2).
+// 267, 534 -> 517; 32^3x64: 875 -> 885, 1612 -> 1580 (4.5 TB/s in k1, 5.4 in k2).
 
 // entry of the link's row: M = (re, im); `re` = the operand of the real part
 // of M v, (re, -im), `im` = that of the imaginary part, (im, re)
@@ -904,7 +904,8 @@ static hipError_t run_g5(const Geom& g, const DslashOp& op, int block, hipStream
     return hipGetLastError();
   } else {
   // several sources: the 18-entry binary16 links serve nothing else, the
-  // 12-entry ones never; FP64 uses the same links
+  // 12-entry ones never; FP64 uses the same links.  The matrix cores take a
+  // site's sources four at a time and split the index by shifts: 4, 8 or 16
   constexpr bool h18 = std::is_base_of<LinkH18, LK>::value, h12 = std::is_same<LK, LinkH12>::value;
   const bool pow2 = (op.nr & (op.nr - 1)) == 0;
   if constexpr (!h12) {
