@@ -211,7 +211,7 @@ int dalloc(T** p, size_t bytes) {
   return QCD_OK;
 }
 
-// The stream has run what was launched on the work set.
+// No iteration is on the stream: a solve waits for its own, also where it fails.
 void drop_graphs(Work& w) {
   for (auto& row : w.iter_graph)
     for (auto& gx : row)
@@ -321,18 +321,9 @@ void free_ctx(qcd_ctx* c) {
   if (c->cap) (void)hipStreamDestroy(c->cap);
 }
 
-// A solve that failed (QCD_ENAN) leaves iterations on the stream, so graphs
-// go only once the stream has run what was launched.
-int drop_graphs(qcd_ctx* c) {
-  bool any = false;
-  for (const Work* w : {&c->w1, &c->wm})
-    for (const auto& row : w->iter_graph)
-      for (const auto& gx : row) any = any || gx != nullptr;
-  if (!any) return QCD_OK;
-  HIPCHK(hipStreamSynchronize(c->stream));
+void drop_graphs(qcd_ctx* c) {
   drop_graphs(c->w1);
   drop_graphs(c->wm);
-  return QCD_OK;
 }
 
 // the site term of k2 reads the compact A_ee where the clover term has its form
@@ -848,8 +839,11 @@ int cg_mixed(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
 }
 
 int run_cg(qcd_ctx* c, const qcd_solver_params* p, CgCounters& cnt) {
-  if (p->prec == QCD_MIXED) return cg_mixed(c, p, cnt);
-  return cg_fp64(c, p, false, cnt);
+  const int rc = p->prec == QCD_MIXED ? cg_mixed(c, p, cnt) : cg_fp64(c, p, false, cnt);
+  // a solve that stops with an error has iterations in flight, whose buffers
+  // and captured graphs the next call may free
+  if (rc != QCD_OK) (void)hipStreamSynchronize(c->stream);
+  return rc;
 }
 
 int validate_params(const qcd_solver_params* p) {
@@ -996,14 +990,15 @@ int qcd_set_params(qcd_ctx* c, double kappa, double csw, int t_boundary) {
   c->tb = t_boundary;
   c->g.tb = t_boundary;
   c->clover_ready = false;
-  return drop_graphs(c);
+  drop_graphs(c);
+  return QCD_OK;
 }
 
 static int clover_copy32(qcd_ctx* c);
 
 int qcd_set_option(qcd_ctx* c, int option, int value) {
   QCHK(check_ctx(c));
-  QCHK(drop_graphs(c));
+  drop_graphs(c);
   switch (option) {
     case QCD_OPT_LINK_RECON:
       if (value != 12 && value != 18) return fail(QCD_EINVAL, "link reconstruction must be 12 or 18");
@@ -1081,7 +1076,7 @@ static int clover_done(qcd_ctx* c) {
   QCHK(clover_copy32(c));
   HIPCHK(hipStreamSynchronize(c->stream));
   const bool compact_ok = c->status_host[1] == 0;
-  if (compact_ok != c->compact_ok) QCHK(drop_graphs(c));  // their k2 reads the other form of A_ee
+  if (compact_ok != c->compact_ok) drop_graphs(c);  // their k2 reads the other form of A_ee
   c->compact_ok = compact_ok;
   if (c->status_host[0] != 0) return fail(QCD_ECLOVER, "an odd-site clover block is not positive definite");
   c->clover_ready = true;
@@ -1209,7 +1204,6 @@ int use_multi(qcd_ctx* c, int n, int prec) {
   if ((long long)c->g.stride * room * 48 >= (1LL << 32))
     return fail(QCD_EINVAL, "too many interleaved right-hand sides for this lattice volume");
   if (c->wm.st == nullptr || c->wm_alloc < room) {
-    if (c->wm.st != nullptr) HIPCHK(hipStreamSynchronize(c->stream));  // a failed solve leaves iterations there
     free_work(c->wm);
     c->wm_alloc = 0;
     QCHK(alloc_work(c->g, c->wm, room, false));

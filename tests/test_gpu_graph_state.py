@@ -22,7 +22,7 @@ def lat():
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 def test_option_after_a_failed_solve(lat, prec):
-    """QCD_ENAN returns with iterations still on the stream; an option dropped their graphs at once."""
+    """QCD_ENAN ends a solve with iterations in flight: they have run before an option destroys their graphs."""
     b = synth.gaussian_source(DIMS, 2, 0)
     bad = b.copy()
     bad[1, 2, 3, 1, 2, 1] = np.nan
